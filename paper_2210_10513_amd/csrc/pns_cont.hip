@@ -200,22 +200,42 @@ __global__ __launch_bounds__(256) void cont_kernel(const ContArgs a)
     const int64_t k0 = a.step[ch];
     int64_t flips = 0, stays = 0;
 
-    auto load_set = [&]() {
+    // New offsets for the groups whose lanes are set in `need` (whole groups;
+    // the same value in every lane).  A group's P pairs (at most 32) are drawn
+    // by 32 lanes of the wave, a pair per lane, two groups at a time, and
+    // handed to the group's lanes by lane reads.  (Drawn by the group's own 8
+    // lanes, each neighbour by itself, a set took ceil(2P / 8) Box-Muller
+    // passes of the whole wave, and each pair was drawn twice: at 25 pairs,
+    // two dimensions and L0 = 1000 about 1030 of the 1545 VALU instructions of
+    // a step, a wave of 8 chains drawing a set in every third step.)
+    auto load_sets = [&](uint64_t need) {
+        while (need != 0) {
+            const int ga = __builtin_ctzll(need);          // first lane of the first group
+            need &= ~(0xFFull << ga);
+            const int gb = need ? __builtin_ctzll(need) : ga;  // and of the second, if there is one
+            need &= ~(0xFFull << gb);
+            const int gl = lane < 32 ? ga : gb;
+            const int pl = lane & 31;
+            const uint32_t qcid = (uint32_t)__shfl((int)cid, gl, 64);
+            const int slo = __shfl((int)(uint32_t)set, gl, 64), shi = __shfl((int)((uint64_t)set >> 32), gl, 64);
+            const int64_t qset = (int64_t)(((uint64_t)(uint32_t)shi << 32) | (uint32_t)slo);
+            const Offset<D> dl = draw_offset<D>(a.seed, qcid, qset, pl);
+            const bool mine = gbase == ga || gbase == gb;
+            const int base = gbase == ga ? 0 : 32;
 #pragma unroll
-        for (int t = 0; t < MP; ++t) {
-            const int j = r * m + t;
-            if (t < m && j < n) {
+            for (int t = 0; t < MP; ++t) {
+                const int j = r * m + t;
                 const int pj = j < P ? j : j - P;
-                const Offset<D> dl = draw_offset<D>(a.seed, cid, set, pj);
+                const bool on = t < m && j < n;
 #pragma unroll
-                for (int i = 0; i < D; ++i) s[t][i] = j < P ? dl.v[i] : -dl.v[i];
-            } else {
-#pragma unroll
-                for (int i = 0; i < D; ++i) s[t][i] = 0.0;
+                for (int i = 0; i < D; ++i) {
+                    const double v = __shfl(dl.v[i], base + (pj & 31), 64);
+                    if (mine) s[t][i] = on ? (j < P ? v : -v) : 0.0;
+                }
             }
         }
     };
-    load_set();
+    load_sets(~0ull);
 
     // lane r keeps estimator sums r, r + 8, ...: weighting idx / NS (M, then
     // the expected multiplicity), component idx % NS (sum w, then w x_i,
@@ -292,7 +312,6 @@ __global__ __launch_bounds__(256) void cont_kernel(const ContArgs a)
             L = a.L0;
             ++set;
             ++stays;
-            load_set();
         } else {
             L -= M;
             // first neighbour whose running sum exceeds U2 * S (weights > 0);
@@ -330,6 +349,7 @@ __global__ __launch_bounds__(256) void cont_kernel(const ContArgs a)
             ++flips;
         }
         if (a.log_cap > 0 && live && r == 0) a.log_action[slot] = action;
+        load_sets(__ballot(stay));
     }
 
     // chain state back to memory
