@@ -19,12 +19,23 @@
 // the first neighbour whose running sum exceeds U2 S).  The per-record scalar work (the multiplicity, the
 // budget, the expected multiplicity) is then shared by 8 chains per wave
 // instruction instead of being repeated by a whole wave for one chain.  The
-// state, its log-density, the budget and the estimator sums stay in registers
-// for the whole launch.  Normal offsets: Box-Muller on two uniforms of one
+// state, its log-density and the budget stay in registers for the whole
+// launch, the estimator sums in LDS (up to three dimensions) or registers.  Normal offsets: Box-Muller on two uniforms of one
 // Philox block, counter (chain, set index low, set index high, 0x80000000 |
 // j << 8 | t) for coordinates 2t, 2t + 1.  Step uniforms: those of the
 // discrete samplers (counter (chain, step low, step high, 0)), drawn 8 steps at
 // a time (lane r of a group holds step k + r).
+//
+// Bound: VALU issue (a wave instruction takes four cycles of its SIMD; the
+// SIMDs issue in over 90% of them).  At d = 2, 25 pairs, L0 = 1000 a step of a
+// wave (8 chains) is about 650 VALU instructions: 7 neighbours of 31, a third
+// of a set drawing of 430, the budget decision, the choice, and an eighth each
+// of the uniforms and of the estimator sums.  65536 chains x 400 records:
+// 4.26 ms (6.1e9 records/s); 8.6 ms at 1545 instructions with each lane
+// drawing its own offsets, log1p and expm1 in every step and a degree-13
+// exponential.  With L0 = 100 and 32 pairs (a set in every step) 7.7 ms
+// against 20.2.  Three waves per SIMD (143 VGPRs); asked for four, the compiler
+// spills 22 registers: 4.28 ms, and 1.05 against 0.95 ms at 2048 chains.
 //
 // Floating-point contraction is off in this file so that the density and the
 // estimator sums round like their plain definitions.
@@ -53,7 +64,7 @@ struct Offset {
 };
 
 template <int D>
-__device__ __noinline__ Offset<D> draw_offset(uint64_t seed, uint32_t cid, int64_t set, int pj)
+__device__ __forceinline__ Offset<D> draw_offset(uint64_t seed, uint32_t cid, int64_t set, int pj)
 {
     Offset<D> o{};
 #pragma unroll
@@ -70,25 +81,23 @@ __device__ __noinline__ Offset<D> draw_offset(uint64_t seed, uint32_t cid, int64
     return o;
 }
 
-// The multiplicity quotient q = log U1 / log(1 - p) (M = 1 + floor(q)) and
-// the expected multiplicity E[min(1 + G, L)] = (1 - (1 - p)^L) / p of a
+// The expected multiplicity E[min(1 + G, L)] = (1 - (1 - p)^L) / p of a
 // budgeted record.  Not inlined: keeps the FP64 library code out of the step
 // loop's registers.
-struct Geo {
-    double q, wrb;
-};
-
-__device__ __noinline__ Geo geometric(double p, double logU1, int64_t L)
+__device__ __forceinline__ double mean_multiplicity(double p, double L)
 {
-    if (p >= 1.0) return {0.0, 1.0};
-    if (p <= 0.0) return {INFINITY, (double)L};
-    const double lg = log1p(-p);
-    return {logU1 / lg, -expm1((double)L * lg) / p};
+    if (p >= 1.0) return 1.0;
+    if (p <= 0.0) return L;
+    return -expm1(L * log1p(-p)) / p;
 }
 
 // Uniforms of step k of chain cid: log U1 (U1 in (0, 1], words 0, 1) and U2
-// in [0, 1) (words 2, 3), returned as (q, wrb) = (log U1, U2).
-__device__ __noinline__ Geo step_uniforms(uint32_t cid, int64_t k, uint64_t seed)
+// in [0, 1) (words 2, 3).
+struct Uniforms {
+    double logU1, U2;
+};
+
+__device__ __forceinline__ Uniforms step_uniforms(uint32_t cid, int64_t k, uint64_t seed)
 {
     const Words o = philox(cid, (uint32_t)k, (uint32_t)((uint64_t)k >> 32), 0u, seed);
     const double u1 = (double)(((((uint64_t)o.w0 << 32) | o.w1) >> 11) + 1u) * 0x1p-53;
@@ -130,45 +139,80 @@ __device__ __forceinline__ double group_scan(double v, int r)
     return v;
 }
 
-// exp(l) for l <= 0 (the weights min(1, pi(y)/pi(x))): Cody-Waite reduction
-// l = k ln 2 + r with |r| <= ln 2 / 2 (ln 2 split in two so that k ln2_hi is
-// exact), exp(r) by its Taylor series to degree 13 (truncation below 2^-57
-// relative) in Horner form, scaled by 2^k with ldexp (gradual underflow; 0
-// below the smallest subnormal).  Within 2 ulp of the correctly rounded
-// value.  The constants are wave-uniform values passed in scalar registers,
-// read once before the step loop.
+// 2^(j/64), j < 64, as the rounded value and the rest (both from the
+// definition in 113-bit arithmetic).
+__device__ const double kExp2[64][2] = {
+    {0x1p+0, 0x0p+0},    {0x1.02c9a3e778061p+0, -0x1.19083535b085dp-56},
+    {0x1.059b0d3158574p+0, 0x1.d73e2a475b465p-55},    {0x1.0874518759bc8p+0, 0x1.186be4bb284ffp-57},
+    {0x1.0b5586cf9890fp+0, 0x1.8a62e4adc610bp-54},    {0x1.0e3ec32d3d1a2p+0, 0x1.03a1727c57b52p-59},
+    {0x1.11301d0125b51p+0, -0x1.6c51039449b3ap-54},    {0x1.1429aaea92dep+0, -0x1.32fbf9af1369ep-54},
+    {0x1.172b83c7d517bp+0, -0x1.19041b9d78a76p-55},    {0x1.1a35beb6fcb75p+0, 0x1.e5b4c7b4968e4p-55},
+    {0x1.1d4873168b9aap+0, 0x1.e016e00a2643cp-54},    {0x1.2063b88628cd6p+0, 0x1.dc775814a8495p-55},
+    {0x1.2387a6e756238p+0, 0x1.9b07eb6c70573p-54},    {0x1.26b4565e27cddp+0, 0x1.2bd339940e9d9p-55},
+    {0x1.29e9df51fdee1p+0, 0x1.612e8afad1255p-55},    {0x1.2d285a6e4030bp+0, 0x1.0024754db41d5p-54},
+    {0x1.306fe0a31b715p+0, 0x1.6f46ad23182e4p-55},    {0x1.33c08b26416ffp+0, 0x1.32721843659a6p-54},
+    {0x1.371a7373aa9cbp+0, -0x1.63aeabf42eae2p-54},    {0x1.3a7db34e59ff7p+0, -0x1.5e436d661f5e3p-56},
+    {0x1.3dea64c123422p+0, 0x1.ada0911f09ebcp-55},    {0x1.4160a21f72e2ap+0, -0x1.ef3691c309278p-58},
+    {0x1.44e086061892dp+0, 0x1.89b7a04ef80dp-59},    {0x1.486a2b5c13cdp+0, 0x1.3c1a3b69062fp-56},
+    {0x1.4bfdad5362a27p+0, 0x1.d4397afec42e2p-56},    {0x1.4f9b2769d2ca7p+0, -0x1.4b309d25957e3p-54},
+    {0x1.5342b569d4f82p+0, -0x1.07abe1db13cadp-55},    {0x1.56f4736b527dap+0, 0x1.9bb2c011d93adp-54},
+    {0x1.5ab07dd485429p+0, 0x1.6324c054647adp-54},    {0x1.5e76f15ad2148p+0, 0x1.ba6f93080e65ep-54},
+    {0x1.6247eb03a5585p+0, -0x1.383c17e40b497p-54},    {0x1.6623882552225p+0, -0x1.bb60987591c34p-54},
+    {0x1.6a09e667f3bcdp+0, -0x1.bdd3413b26456p-54},    {0x1.6dfb23c651a2fp+0, -0x1.bbe3a683c88abp-57},
+    {0x1.71f75e8ec5f74p+0, -0x1.16e4786887a99p-55},    {0x1.75feb564267c9p+0, -0x1.0245957316dd3p-54},
+    {0x1.7a11473eb0187p+0, -0x1.41577ee04992fp-55},    {0x1.7e2f336cf4e62p+0, 0x1.05d02ba15797ep-56},
+    {0x1.82589994cce13p+0, -0x1.d4c1dd41532d8p-54},    {0x1.868d99b4492edp+0, -0x1.fc6f89bd4f6bap-54},
+    {0x1.8ace5422aa0dbp+0, 0x1.6e9f156864b27p-54},    {0x1.8f1ae99157736p+0, 0x1.5cc13a2e3976cp-55},
+    {0x1.93737b0cdc5e5p+0, -0x1.75fc781b57ebcp-57},    {0x1.97d829fde4e5p+0, -0x1.d185b7c1b85d1p-54},
+    {0x1.9c49182a3f09p+0, 0x1.c7c46b071f2bep-56},    {0x1.a0c667b5de565p+0, -0x1.359495d1cd533p-54},
+    {0x1.a5503b23e255dp+0, -0x1.d2f6edb8d41e1p-54},    {0x1.a9e6b5579fdbfp+0, 0x1.0fac90ef7fd31p-54},
+    {0x1.ae89f995ad3adp+0, 0x1.7a1cd345dcc81p-54},    {0x1.b33a2b84f15fbp+0, -0x1.2805e3084d708p-57},
+    {0x1.b7f76f2fb5e47p+0, -0x1.5584f7e54ac3bp-56},    {0x1.bcc1e904bc1d2p+0, 0x1.23dd07a2d9e84p-55},
+    {0x1.c199bdd85529cp+0, 0x1.11065895048ddp-55},    {0x1.c67f12e57d14bp+0, 0x1.2884dff483cadp-54},
+    {0x1.cb720dcef9069p+0, 0x1.503cbd1e949dbp-56},    {0x1.d072d4a07897cp+0, -0x1.cbc3743797a9cp-54},
+    {0x1.d5818dcfba487p+0, 0x1.2ed02d75b3707p-55},    {0x1.da9e603db3285p+0, 0x1.c2300696db532p-54},
+    {0x1.dfc97337b9b5fp+0, -0x1.1a5cd4f184b5cp-54},    {0x1.e502ee78b3ff6p+0, 0x1.39e8980a9cc8fp-55},
+    {0x1.ea4afa2a490dap+0, -0x1.e9c23179c2893p-54},    {0x1.efa1bee615a27p+0, 0x1.dc7f486a4b6bp-54},
+    {0x1.f50765b6e454p+0, 0x1.9d3e12dd8a18bp-54},    {0x1.fa7c1819e90d8p+0, 0x1.74853f3a5931ep-55},
+};
+
+// exp(l) for l <= 0 (the weights min(1, pi(y)/pi(x))): l = (k / 64) ln 2 + r
+// with |r| <= ln 2 / 128 (ln 2 / 64 split in two so that k times its first
+// part is exact), exp(r) - 1 by its Taylor series to degree 6 (truncation
+// below 2^-64), times 2^((k mod 64) / 64) from the table in LDS with its low
+// part, scaled by ldexp (gradual underflow; 0 below the smallest subnormal).
+// At most 0.512 ulp off over [-700, 0] (3e6 random arguments against 113-bit
+// values), where the series to degree 13 without a table, 7 more FP64
+// operations and 10 more constants, was 0.87 ulp off.
+// Its constants are wave-uniform values in scalar registers (the first in a
+// vector register: one scalar operand per instruction), made opaque so that
+// they are not moved to vector registers for each use.
 struct ExpConsts {
-    double c[14];  // 1 / j!
-    double log2e, ln2_hi, ln2_lo;
+    double c6, c5, c4, c3, log2e, ln2_hi, ln2_lo;
 };
 
 __device__ __forceinline__ ExpConsts exp_consts()
 {
-    ExpConsts e;
-    double f = 1.0;
-#pragma unroll
-    for (int j = 0; j < 14; ++j) {
-        if (j > 0) f = f / (double)j;
-        e.c[j] = f;
-    }
-    e.log2e = 0x1.71547652b82fep+0;
-    e.ln2_hi = 0x1.62e42fee00000p-1;
-    e.ln2_lo = 0x1.a39ef35793c76p-33;
-#pragma unroll
-    for (int j = 0; j < 14; ++j) asm volatile("" : "+s"(e.c[j]));
+    ExpConsts e{1.0 / 720.0, 1.0 / 120.0, 1.0 / 24.0, 1.0 / 6.0, 0x1.71547652b82fep+6, -0x1.62e42fee00000p-7,
+                -0x1.a39ef35793c76p-39};
+    asm volatile("" : "+v"(e.c6), "+s"(e.c5), "+s"(e.c4), "+s"(e.c3));
     asm volatile("" : "+s"(e.log2e), "+s"(e.ln2_hi), "+s"(e.ln2_lo));
     return e;
 }
 
-__device__ __forceinline__ double exp_nonpos(double l, const ExpConsts& e)
+__device__ __forceinline__ double exp_nonpos(double l, const double (*tab)[2], const ExpConsts& e)
 {
     l = fmax(l, -746.0);
     const double k = rint(l * e.log2e);
-    const double r = fma(-k, e.ln2_lo, fma(-k, e.ln2_hi, l));
-    double p = e.c[13];
-#pragma unroll
-    for (int j = 12; j >= 0; --j) p = fma(p, r, e.c[j]);
-    return ldexp(p, (int)k);
+    const double r = fma(k, e.ln2_lo, fma(k, e.ln2_hi, l));
+    const int ki = (int)k;
+    const double* t = tab[ki & 63];
+    double p = fma(r, e.c6, e.c5);
+    p = fma(r, p, e.c4);
+    p = fma(r, p, e.c3);
+    p = fma(r, p, 0.5);
+    p = fma(r * r, p, r);
+    return ldexp(t[0] + fma(t[0], p, t[1]), ki >> 6);
 }
 
 // MP: neighbours per lane the kernel is built for (m <= MP; the launcher
@@ -178,6 +222,9 @@ __device__ __forceinline__ double exp_nonpos(double l, const ExpConsts& e)
 template <int D, int MP>
 __global__ __launch_bounds__(256) void cont_kernel(const ContArgs a)
 {
+    __shared__ double etab[64][2];
+    if (threadIdx.x < 128) etab[threadIdx.x >> 1][threadIdx.x & 1] = kExp2[threadIdx.x >> 1][threadIdx.x & 1];
+    __syncthreads();
     const int lane = threadIdx.x & 63;
     const int r = lane & (kGroup - 1);            // lane within the chain's group
     const int gbase = lane & ~(kGroup - 1);       // first lane of the group
@@ -191,6 +238,13 @@ __global__ __launch_bounds__(256) void cont_kernel(const ContArgs a)
     const uint32_t cid = a.chain_id[ch];
     constexpr int NS = 4 * D + 1;                 // estimator sums per weighting
     constexpr int NA = (2 * NS + kGroup - 1) / kGroup;  // sums per lane
+    // The estimator sums of 8 steps together, lane r of a group for step r of
+    // the eight, into sums of its own over the launch, added up over the group
+    // at its end: the expected multiplicity (log1p, expm1, a division) and the
+    // sums are then formed once per 8 steps instead of by every lane in every
+    // step.  Above three dimensions the 2 (4 D + 1) sums of a lane would not
+    // fit the registers, and the lanes share one set.
+    constexpr bool kDefer = D <= 3;
 
     double x[D], s[MP][D], w[MP];
 #pragma unroll
@@ -240,17 +294,53 @@ __global__ __launch_bounds__(256) void cont_kernel(const ContArgs a)
     // lane r keeps estimator sums r, r + 8, ...: weighting idx / NS (M, then
     // the expected multiplicity), component idx % NS (sum w, then w x_i,
     // w x_i^2, w x_i^4, w 1(x_i > 0))
+    // (kDefer, up to three dimensions: every lane keeps all of them, over the
+    // records of its own steps, see below)
+    __shared__ double dsum[kDefer ? 2 * NS : 1][kDefer ? 256 : 1];
     double acc[NA];
     int akind[NA], agrp[NA], aci[NA];
+    double dx[kDefer ? D : 1], dM = 0.0, dp = 1.0, dL = 0.0;
+    int dcnt = 0;
+    if constexpr (kDefer) {
 #pragma unroll
-    for (int u = 0; u < NA; ++u) {
-        const int idx = r + kGroup * u;
-        akind[u] = idx < 2 * NS ? idx / NS : -1;
-        const int comp = idx % NS;
-        agrp[u] = comp == 0 ? -1 : (comp - 1) / D;
-        aci[u] = comp == 0 ? 0 : (comp - 1) % D;
-        acc[u] = akind[u] >= 0 ? a.sums[(int64_t)ch * 2 * NS + idx] : 0.0;
+        for (int u = 0; u < 2 * NS; ++u) dsum[u][threadIdx.x] = 0.0;
+#pragma unroll
+        for (int i = 0; i < D; ++i) dx[i] = 0.0;
+    } else {
+#pragma unroll
+        for (int u = 0; u < NA; ++u) {
+            const int idx = r + kGroup * u;
+            akind[u] = idx < 2 * NS ? idx / NS : -1;
+            const int comp = idx % NS;
+            agrp[u] = comp == 0 ? -1 : (comp - 1) / D;
+            aci[u] = comp == 0 ? 0 : (comp - 1) % D;
+            acc[u] = akind[u] >= 0 ? a.sums[(int64_t)ch * 2 * NS + idx] : 0.0;
+        }
     }
+    // Sums of the records kept by the lanes (lane r: step kb + r, r < dcnt).
+    auto flush = [&](int64_t kb) {
+        const double wrb = mean_multiplicity(dp, dL);
+        const bool on = r < dcnt;
+        const double wM = on ? dM : 0.0, wR = on ? wrb : 0.0;
+        auto add = [&](int u, double v) { dsum[kDefer ? u : 0][kDefer ? threadIdx.x : 0] += v; };
+        add(0, wM);
+        add(NS, wR);
+#pragma unroll
+        for (int i = 0; i < (kDefer ? D : 0); ++i) {
+            const double v = dx[i], v2 = v * v, v4 = v2 * v2;
+            add(1 + i, wM * v);
+            add(NS + 1 + i, wR * v);
+            add(1 + D + i, wM * v2);
+            add(NS + 1 + D + i, wR * v2);
+            add(1 + 2 * D + i, wM * v4);
+            add(NS + 1 + 2 * D + i, wR * v4);
+            add(1 + 3 * D + i, v > 0.0 ? wM : 0.0);
+            add(NS + 1 + 3 * D + i, v > 0.0 ? wR : 0.0);
+        }
+        // (a ring shorter than the batch keeps its last records)
+        if (a.log_cap > 0 && live && on && r + a.log_cap >= dcnt)
+            a.log_w[(int64_t)ch * a.log_cap + (kb + r) % a.log_cap] = wrb;
+    };
 
     const ExpConsts ek = exp_consts();
     double logU1b = 0.0, U2b = 0.0;
@@ -258,9 +348,12 @@ __global__ __launch_bounds__(256) void cont_kernel(const ContArgs a)
         const int64_t k = k0 + it;
         const int bl = (int)(it & (kGroup - 1));
         if (bl == 0) {
-            const Geo u = step_uniforms(cid, k + r, a.seed);
-            logU1b = u.q;
-            U2b = u.wrb;
+            if constexpr (kDefer) {
+                if (it > 0) flush(k - kGroup);
+            }
+            const Uniforms u = step_uniforms(cid, k + r, a.seed);
+            logU1b = u.logU1;
+            U2b = u.U2;
         }
         // weights of this lane's neighbours, min(1, pi(y)/pi(x)) = exp(min(l, 0))
         // (exp(0) = 1 exactly), summed in neighbour order
@@ -272,30 +365,47 @@ __global__ __launch_bounds__(256) void cont_kernel(const ContArgs a)
             for (int i = 0; i < D; ++i) y[i] = x[i] + s[t][i];
             const double l = fmin(log_density<D>(y, a.mu0, a.c) - lpx, 0.0);
             const bool on = t < m && r * m + t < n;
-            w[t] = on ? exp_nonpos(l, ek) : 0.0;
+            w[t] = on ? exp_nonpos(l, etab, ek) : 0.0;
             ls += w[t];
         }
         const double incl = group_scan(ls, r);
         const double S = __shfl(incl, gbase + kGroup - 1, 64);
         const double p = S / (double)n;
         const double logU1 = __shfl(logU1b, gbase + bl, 64), U2 = __shfl(U2b, gbase + bl, 64);
-        const Geo g = geometric(p, logU1, L);
-        const bool stay = g.q >= (double)L;
-        const int64_t M = stay ? L : (int64_t)floor(g.q) + 1;
+        // (the estimate of the step kernel: the exact logarithm only where it
+        // cannot tell the floor or the order against L)
+        double q;
+        if (p >= 1.0) q = 0.0;
+        else if (p <= 0.0) q = INFINITY;
+        else q = step::geometric_quotient(logU1, p, (double)L);
+        const bool stay = q >= (double)L;
+        const int64_t M = stay ? L : (int64_t)floor(q) + 1;
 
         // the record (J_k, M_k): estimator sums over the state before the move
+        double wrb = 0.0;
+        if constexpr (kDefer) {
+            const bool keep = r == bl;
 #pragma unroll
-        for (int u = 0; u < NA; ++u) {
-            if (akind[u] < 0) continue;
-            const double wt = akind[u] == 0 ? (double)M : g.wrb;
-            if (agrp[u] < 0) {
-                acc[u] += wt;
-            } else {
-                const double v = pick<D>(x, aci[u]), v2 = v * v;
-                if (agrp[u] == 0) acc[u] += wt * v;
-                else if (agrp[u] == 1) acc[u] += wt * v2;
-                else if (agrp[u] == 2) acc[u] += wt * (v2 * v2);
-                else acc[u] += v > 0.0 ? wt : 0.0;
+            for (int i = 0; i < D; ++i) dx[i] = keep ? x[i] : dx[i];
+            dM = keep ? (double)M : dM;
+            dp = keep ? p : dp;
+            dL = keep ? (double)L : dL;
+            dcnt = bl + 1;
+        } else {
+            wrb = mean_multiplicity(p, (double)L);
+#pragma unroll
+            for (int u = 0; u < NA; ++u) {
+                if (akind[u] < 0) continue;
+                const double wt = akind[u] == 0 ? (double)M : wrb;
+                if (agrp[u] < 0) {
+                    acc[u] += wt;
+                } else {
+                    const double v = pick<D>(x, aci[u]), v2 = v * v;
+                    if (agrp[u] == 0) acc[u] += wt * v;
+                    else if (agrp[u] == 1) acc[u] += wt * v2;
+                    else if (agrp[u] == 2) acc[u] += wt * (v2 * v2);
+                    else acc[u] += v > 0.0 ? wt : 0.0;
+                }
             }
         }
         const int64_t slot = (int64_t)ch * a.log_cap + (a.log_cap > 0 ? k % a.log_cap : 0);
@@ -303,7 +413,7 @@ __global__ __launch_bounds__(256) void cont_kernel(const ContArgs a)
             a.log_M[slot] = M;
             a.log_lp[slot] = lpx;
             a.log_p[slot] = p;
-            a.log_w[slot] = g.wrb;
+            if constexpr (!kDefer) a.log_w[slot] = wrb;
         }
         int32_t action;
         if (stay) {
@@ -352,12 +462,26 @@ __global__ __launch_bounds__(256) void cont_kernel(const ContArgs a)
         load_sets(__ballot(stay));
     }
 
+    if constexpr (kDefer) {
+        if (dcnt > 0) flush(k0 + a.steps - dcnt);
+    }
+
     // chain state back to memory
     if (!live) return;
     if (r < D) a.x[(int64_t)chain * D + r] = pick<D>(x, r);
+    if constexpr (kDefer) {
 #pragma unroll
-    for (int u = 0; u < NA; ++u)
-        if (akind[u] >= 0) a.sums[(int64_t)chain * 2 * NS + r + kGroup * u] = acc[u];
+        for (int u = 0; u < 2 * NS; ++u) {
+            double t = dsum[u][threadIdx.x];
+#pragma unroll
+            for (int d = 1; d < kGroup; d <<= 1) t += __shfl_xor(t, d, 64);
+            if (r == (u & (kGroup - 1))) a.sums[(int64_t)chain * 2 * NS + u] += t;
+        }
+    } else {
+#pragma unroll
+        for (int u = 0; u < NA; ++u)
+            if (akind[u] >= 0) a.sums[(int64_t)chain * 2 * NS + r + kGroup * u] = acc[u];
+    }
     if (r == 0) {
         a.lpx[chain] = lpx;
         a.L[chain] = L;

@@ -145,3 +145,23 @@ def test_estimators_match_the_donut_moments(d, sigma):
             se = v.std(0, ddof=1) / np.sqrt(C)
             z = np.abs(v.mean(0) - want[k]) / se
             assert (z < 5).all(), (row, k, z)
+
+
+@pytest.mark.parametrize("d,K,ring", [(1, 5, 9), (2, 13, 3), (3, 16, 8), (3, 17, 1), (4, 13, 3)])
+def test_log_ring_shorter_than_a_batch_of_steps(d, K, ring):
+    """The expected multiplicities of up to eight steps are formed together
+    (up to three dimensions): runs that end inside a batch, and log rings
+    shorter than one, keep the last records of the run."""
+    from paper_2210_10513_amd.binding import ContSampler
+    x0 = inputs.donut_draws(9, d, 9.0, 0.5, seed=d)
+    kw = dict(mu0=9.0, sigma=0.5, pairs=5, L0=30, seed=8)
+    s = ContSampler(9, dim=d, x0=x0, log_capacity=ring, **kw)
+    s.run(K)
+    g, sums = s.read_log(), s.read_sums()
+    s.close()
+    o = _oracle(x0, K, **kw)
+    assert np.allclose(sums, o.sums, rtol=X_RTOL, atol=X_RTOL)
+    for k in range(max(0, K - ring), K):
+        assert np.array_equal(g["action"][:, k % ring], o.action[:, k])
+        assert np.array_equal(g["M"][:, k % ring], o.M[:, k])
+        assert np.allclose(g["w"][:, k % ring], o.w[:, k], rtol=P_RTOL, atol=0)
