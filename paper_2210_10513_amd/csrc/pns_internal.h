@@ -92,7 +92,16 @@ struct InitArgs {
     void* h;
     int64_t* E;
     int64_t* last_E;
+    void* fields_ws;                // row data of a float matrix (fields_ws_bytes), else unused
 };
+
+// Fields h of the chains [cbeg, cend), all of one problem of the given pitch,
+// from their states: one matrix product.  fields_ws_bytes: bytes of
+// InitArgs::fields_ws for float problems of up to N variables (calls queued on
+// one stream may share it).
+size_t fields_ws_bytes(int64_t N);
+hipError_t launch_fields(int32_t qtype, int32_t htype, int64_t pitch, const InitArgs& a, int32_t cbeg, int32_t cend,
+                         hipStream_t st);
 
 // Step kernel launch for one (block, groups) tile shape, field type and Q
 // type.  flav: 0 every bit, 1 systematic window, 2 random subset drawn in

@@ -474,6 +474,7 @@ struct pns_ctx {
     uint32_t* chain_id = nullptr;
     uint8_t* x = nullptr;
     void* h = nullptr;
+    uint8_t* fields_ws = nullptr;  // workspace of the field products (float problems)
     uint8_t* rmem = nullptr;
     int64_t* E = nullptr;
     int64_t* L = nullptr;
@@ -669,7 +670,7 @@ struct pns_ctx {
         if (graph) (void)hipGraphDestroy(graph);
         for (hipEvent_t ev : prof_ev)
             if (ev) (void)hipEventDestroy(ev);
-        void* ptrs[] = {problems, chain_problem, foff, beta, chain_id, x, h, rmem, E, L, sub, step, last_action, last_M,
+        void* ptrs[] = {problems, chain_problem, foff, beta, chain_id, x, h, fields_ws, rmem, E, L, sub, step, last_action, last_M,
                         last_E, counters, log_action, log_M, log_E, log_p, log_w, hist_w, hist_v, hist_rb,
                         snap_x, snap_M, snap_E, snap_w, snap_count};
         for (void* p : ptrs)
@@ -923,6 +924,7 @@ int create_impl(pns_ctx** out, std::vector<ProblemSpec>& specs, int32_t mode, co
     ALLOC(ctx->chain_id, uint32_t, C);
     ALLOC(ctx->x, uint8_t, fields);
     ALLOC(ctx->h, uint8_t, fields * hbytes);
+    if (qtype == Q_F32) ALLOC(ctx->fields_ws, uint8_t, fields_ws_bytes(ctx->max_pitch));
     ALLOC(ctx->E, int64_t, C);
     ALLOC(ctx->L, int64_t, C);
     ALLOC(ctx->sub, int64_t, C);
@@ -1065,6 +1067,7 @@ int create_impl(pns_ctx** out, std::vector<ProblemSpec>& specs, int32_t mode, co
         ia.chain_id = ctx->chain_id;
         ia.x = ctx->x;
         ia.h = ctx->h;
+        ia.fields_ws = ctx->fields_ws;
         ia.E = ctx->E;
         ia.last_E = ctx->last_E;
         e = launch_init_with_map(qtype, htype, (int32_t)ctx->max_pitch, ctx->stream, ia, ctx->h_chain_problem.data(),
@@ -2184,6 +2187,7 @@ int pns_set_q(pns_ctx* ctx, int32_t problem, const void* Q)
     ia.chain_id = ctx->chain_id + c0;
     ia.x = ctx->x;
     ia.h = ctx->h;
+    ia.fields_ws = ctx->fields_ws;
     ia.E = ctx->E + c0;
     ia.last_E = ctx->last_E + c0;
     e = launch_init_with_map(ctx->qtype, ctx->htype, (int32_t)R.pitch, st, ia, ctx->h_chain_problem.data() + c0,
@@ -2321,6 +2325,7 @@ int pns_adopt_best(pns_ctx* ctx)
     ia.chain_id = ctx->chain_id;
     ia.x = ctx->x;
     ia.h = ctx->h;
+    ia.fields_ws = ctx->fields_ws;
     ia.E = ctx->E;
     ia.last_E = ctx->last_E;
     hipError_t e = launch_init_with_map(ctx->qtype, ctx->htype, (int32_t)ctx->max_pitch, st, ia,
@@ -2438,6 +2443,7 @@ extern "C" int pns_refresh(pns_ctx* ctx)
     ia.chain_id = ctx->chain_id;
     ia.x = ctx->x;
     ia.h = ctx->h;
+    ia.fields_ws = ctx->fields_ws;
     ia.E = ctx->E;
     ia.last_E = nullptr;  // the last record keeps its energy
     hipError_t e = launch_init_with_map(ctx->qtype, ctx->htype, (int32_t)ctx->max_pitch, ctx->stream, ia,

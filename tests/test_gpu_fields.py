@@ -125,3 +125,40 @@ def test_set_q_fields_are_the_new_product():
     s.set_q(Q2)
     _check(s.read_current(), Q2)
     s.close()
+
+
+@pytest.mark.parametrize("rest", [0, 1, 31, 32, 33, "all"])
+@pytest.mark.parametrize("N,chains", [(40, 3), (130, 129), (1100, 257)])
+def test_float_entries_below_the_rows_unit(N, chains, rest):
+    """Float entries are products of 39-bit integers in units of their row's
+    scale; entries with bits below it go through a list of at most 32 per row,
+    rows with more of them through the FP64 product, and rows of zeros and of
+    subnormal entries have scales of their own.  Bound: the rounding of the
+    list's sums (33 additions) or of the FP64 product's (N additions)."""
+    import math
+    from paper_2210_10513_amd.binding import Sampler
+    rng = np.random.default_rng(N)
+    Q = inputs.symmetric_gauss(N, seed=N)
+    Q[np.abs(Q) < 2.0 ** -9 * np.abs(Q).max()] = 0.5  # nothing below the unit
+    if rest == "all":
+        Q = (np.sign(Q) * np.exp2(rng.uniform(-60, 60, size=(N, N)))).astype(np.float32)
+        Q = np.triu(Q) + np.triu(Q, 1).T
+    else:
+        for i in rng.choice(np.arange(3, N), size=3, replace=False):
+            js = rng.choice(np.delete(np.arange(N), i), size=min(rest, N - 1), replace=False)
+            Q[i, js] = Q[js, i] = np.float32(1.0 / 3.0) * np.exp2(rng.integers(-40, -20, size=len(js))).astype(np.float32)
+        Q[0, 1:] = Q[1:, 0] = 0.0
+        Q[1, 2:] = Q[2:, 1] = 0.0
+        Q[1, 2] = Q[2, 1] = np.float32(1e-42)
+    x = rng.integers(0, 2, size=(chains, N)).astype(np.uint8)
+    s = Sampler(Q, 1e-9, 0, "rf", num_chains=chains, x0=x)
+    h = s.read_current()["h"]
+    s.close()
+    A = Q.astype(np.float64)
+    np.fill_diagonal(A, 0.0)
+    few = rest != "all" and rest <= 32
+    for c in range(0, chains, 16):
+        on = A[:, x[c] != 0]
+        for f in range(N):
+            bound = (34 if few else N) * 2.0 ** -53 * np.abs(on[f]).sum()
+            assert abs(h[c, f] - math.fsum(on[f])) <= bound, (c, f)
