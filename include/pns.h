@@ -535,14 +535,9 @@ int pns_load(pns_ctx* ctx, const void* buf, int64_t size);
  *          G and sum_m all in device memory the call only queues work;
  *          any host buffer makes it synchronise the stream before it
  *          returns.
- * Computed on the bf16 matrix cores with FP32 accumulation: x is exact in
- * bf16 and each m_k is split into up to three bf16 pieces (exact for
- * m_k < 2^24), so every product is an exact integer.  The FP32
- * accumulators are added into G (FP64) every F records with
- * F * max(m) < 2^24 (F >= 64), so G is exact whenever m_k <= 2^18 for
- * every k; beyond that each partial sum carries a relative error below
- * 64 * 2^-24 and, for m_k >= 2^24, the weight itself is rounded to 24
- * bits.
+ * Computed on the int8 matrix cores: x as 0/1 bytes, m_k as digits base 128,
+ * exact int32 sums per digit, put together in FP64: G is exact while every
+ * entry is below 2^53 (beyond that each addition of a partial sum rounds once).
  * Errors: PNS_EINVAL (NULL X, m or G, N outside [1, 32768], K < 0,
  * ldx < N), PNS_ENOMEM, PNS_EDEVICE.
  */

@@ -174,19 +174,28 @@ int set_error(int code, const char* fmt, ...);
 namespace pns {
 
 // Differentiation path (pns_moments.hip).
-// Weight pieces (3 x kpad bf16), exact sum and max of the weights.
-hipError_t launch_moments_prep(const int64_t* m, int64_t K, int64_t kpad, uint16_t* pieces, unsigned long long* sum_m,
-                               unsigned long long* max_m, hipStream_t st);
+// G = X^T diag(m) X with integer weights (times -beta / sum m if scaled), the
+// sum of the weights to *sum unless NULL; `ws` holds w.bytes.
+struct MomentsWorkspace {
+    int32_t npad;                                // columns: N rounded up to 64
+    int64_t steps, tiles, chunk_steps;           // steps of 64 records, 64 x 64 tiles, steps per workgroup
+    int64_t digits, ndig, psum, part, bytes;     // offsets of the arrays after the packed records; size
+};
+// limit > 0: at most that many bytes, if one partial tile per tile fits.
+MomentsWorkspace moments_int_workspace(int64_t K, int32_t N, int64_t limit);
+hipError_t launch_moments_int(const uint8_t* X, int64_t ldx, const int64_t* m, int64_t K, int32_t N, double* G,
+                              double* sum, bool scaled, double beta, const MomentsWorkspace& w, void* ws,
+                              hipStream_t st);
+// Real weights:
 // Records X [K][ldx] bytes -> column-packed bits Xb [words][npad] u32,
 // words = ceil(K / 32), npad = N rounded up to 64.
 hipError_t launch_pack_bits(const uint8_t* X, int64_t ldx, int64_t K, int32_t N, int32_t npad, int64_t words,
                             uint32_t* Xb, hipStream_t st);
-// G += X^T diag(m) X from packed records: one wave per (64 x 64 tile of the
+// G += X^T diag(w) X from packed records: one wave per (64 x 64 tile of the
 // upper triangle, chunk of chunk_words words), partial tiles in `part`
 // [chunks][tiles][64][64] FP32, then an FP64 reduction into G.
 hipError_t launch_moments(const uint32_t* Xb, int32_t npad, int64_t words, int32_t N, const uint16_t* pieces,
-                          int64_t kpad, int64_t chunk_words, const unsigned long long* max_m, float* part, double* G,
-                          hipStream_t st);
+                          int64_t kpad, int64_t chunk_words, float* part, double* G, hipStream_t st);
 // ---- continuous Unbiased PNS (Alg 7, donut target) ----
 struct ContArgs {
     int32_t dim;                    // 1 .. 7
@@ -223,8 +232,6 @@ hipError_t launch_moments_prep_f64(const double* w, int64_t K, int64_t kpad, uin
                                    unsigned long long* maxbits, hipStream_t st);
 // G[0..n) *= 2^ilogb(max): undoes the weight scaling of launch_moments_prep_f64.
 hipError_t launch_moments_unscale(double* G, int64_t n, const unsigned long long* maxbits, hipStream_t st);
-// *out = (double)*sum_m on the device.
-hipError_t launch_moments_sum(const unsigned long long* sum_m, double* out, hipStream_t st);
 // log Z by enumeration: `blocks` x 256 threads, thread t covers the states
 // with high bits t and all 2^lowbits low bits; part_* hold `blocks` pairs.
 hipError_t launch_logz(int32_t qtype, const void* Q, int32_t N, int32_t layout, double beta, double* part_max,

@@ -3,12 +3,12 @@
 // * Multiplicity-weighted second moments G = X^T diag(m) X of jump-chain
 //   records (x_k, m_k): the estimate of E_pi[x x^T] (times sum_k m_k) whose
 //   product with -beta is grad_Q log Z.  Dense contraction over the records
-//   on the bf16 matrix cores (v_mfma_f32_16x16x32_bf16) with FP32
-//   accumulation: x is 0/1 (exact in bf16) and each m_k is split into up to
-//   three bf16 pieces that sum to it (exact for m_k < 2^24), so every product
-//   is exact and an FP32 partial sum is exact while it stays below 2^24; the
-//   records are cut into chunks short enough for that, and chunk results are
-//   added into FP64.
+//   on the matrix cores.  Integer weights: v_mfma_i32_16x16x64_i8, x as 0/1
+//   bytes and m_k as digits base 128, a pass over the records per digit (the
+//   first digit of all of them, a further one only of the steps of 64 records
+//   that have it), so that every sum is exact.  Real weights:
+//   v_mfma_f32_16x16x32_bf16 with FP32 accumulation, each weight split into
+//   three bf16 pieces.
 // * log Z = log sum_x exp(-beta x^T Q x) by enumeration of all 2^N states
 //   (N <= 32) in Gray-code order with an incremental energy, FP64
 //   log-sum-exp.
@@ -25,6 +25,7 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
 
 // Round-to-nearest-even of a float to bf16 (bit pattern).
 __device__ __forceinline__ uint16_t bf16_bits(float f)
@@ -36,53 +37,39 @@ __device__ __forceinline__ uint16_t bf16_bits(float f)
 
 __device__ __forceinline__ float bf16_value(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
-// Pieces of each weight (m = p0 + p1 + p2, each a bf16) and the exact sum
-// and maximum of the weights.  Pieces are stored [3][kpad], zero past K.
-// Grid-stride loop; one atomic per workgroup for the sum and the maximum.
-__global__ __launch_bounds__(256) void moments_prep_kernel(const int64_t* m, int64_t K, int64_t kpad, uint16_t* pieces,
-                                                           unsigned long long* sum_m, unsigned long long* max_m)
+// Digits of integer weights, base 128, and their sum.  A step is 64 records;
+// digit d of the step's weights is 64 bytes of digits[d], in the order of the
+// operand bytes of moments_i8_kernel, and ndig[step] says how many digits the
+// step's largest weight has (the others are not written).  Negative weights
+// count as 0.  One wave per step; each workgroup's sum goes to psum[block].
+constexpr int kDigits = 9;  // 63 bits, 7 bits each
+
+__device__ void weight_digits(const int64_t* __restrict__ m, int64_t K, int64_t steps, uint8_t* __restrict__ digits,
+                              uint8_t* __restrict__ ndig, unsigned long long* __restrict__ psum, int block, int blocks)
 {
-    __shared__ unsigned long long red[2][4];
-    const int64_t n = kpad > K ? kpad : K;
-    unsigned long long sv = 0, mv = 0;
-    for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (int64_t)gridDim.x * blockDim.x) {
-        int64_t mk = 0;
-        if (k < K) mk = m[k] > 0 ? m[k] : 0;
-        if (k < kpad) {
-            // m < 2^24 is exact in float; the pieces then sum to it exactly
-            float r = (float)mk;
-            uint16_t b[3];
-#pragma unroll
-            for (int s = 0; s < 3; ++s) {
-                b[s] = bf16_bits(r);
-                r = r - bf16_value(b[s]);
-            }
-#pragma unroll
-            for (int s = 0; s < 3; ++s) pieces[s * kpad + k] = b[s];
-        }
-        sv += (unsigned long long)mk;
-        mv = mv > (unsigned long long)mk ? mv : (unsigned long long)mk;
+    __shared__ unsigned long long red[4];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    // byte of record `lane` of a step: of word lane / 32 of a column, operand
+    // lane group kg and register j take the bits 4 (kg % 2) + j + 8 b
+    const int bit = lane & 31, word = lane >> 5;
+    const int pos = (word * 2 + ((bit & 7) >> 2)) * 16 + (bit & 3) * 4 + (bit >> 3);
+    unsigned long long sum = 0;
+    for (int64_t st = (int64_t)block * 4 + wave; st < steps; st += (int64_t)blocks * 4) {
+        const int64_t k = st * 64 + lane;
+        const int64_t mk = k < K && m[k] > 0 ? m[k] : 0;
+        sum += (unsigned long long)mk;
+        int nd = 0;
+        do {
+            digits[(int64_t)nd * steps * 64 + st * 64 + pos] = (uint8_t)((uint64_t)mk >> (7 * nd) & 127u);
+            ++nd;
+        } while (nd < kDigits && __ballot(((uint64_t)mk >> (7 * nd)) != 0) != 0);
+        if (lane == 0) ndig[st] = (uint8_t)nd;
     }
 #pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-        sv += __shfl_xor(sv, d, 64);
-        const unsigned long long o = __shfl_xor(mv, d, 64);
-        mv = mv > o ? mv : o;
-    }
-    if ((threadIdx.x & 63) == 0) {
-        red[0][threadIdx.x >> 6] = sv;
-        red[1][threadIdx.x >> 6] = mv;
-    }
+    for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, 64);
+    if (lane == 0) red[wave] = sum;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        unsigned long long ts = 0, tm = 0;
-        for (int w = 0; w < (int)(blockDim.x >> 6); ++w) {
-            ts += red[0][w];
-            tm = tm > red[1][w] ? tm : red[1][w];
-        }
-        atomicAdd(sum_m, ts);
-        atomicMax(max_m, tm);
-    }
+    if (threadIdx.x == 0) psum[block] = red[0] + red[1] + red[2] + red[3];
 }
 
 // Real (FP64) weights, e.g. the expected multiplicities 1 / p of Thm 3 (5).
@@ -177,61 +164,238 @@ __device__ __forceinline__ void upper_tile(int t, int nt, int* ti, int* tj)
 }
 
 // Records packed column by column: word (w, i) holds bit r = X[32 w + r][i]
-// (zero past K), so the eight records a lane feeds to one MFMA step are one
-// byte of one word.  One thread per (column, word).
-__global__ void pack_bits_kernel(const uint8_t* __restrict__ X, int64_t ldx, int64_t K, int32_t N, int32_t npad,
-                                 int64_t words, uint32_t* __restrict__ Xb)
+// (zero past K), so the records a lane feeds to one MFMA step are bits of one
+// word.  One thread per word and column, or four columns (VEC: one 32-bit load
+// per record, rows 4-byte aligned: ldx % 4 == 0 and X aligned; npad % 4 == 0).
+// The 32 loads of a whole word are issued together.  Bound: the records'
+// bytes, read once.
+template <bool VEC>
+__device__ void pack_columns(const uint8_t* __restrict__ X, int64_t ldx, int64_t K, int32_t N, int32_t npad,
+                             int64_t words, uint32_t* __restrict__ Xb, int64_t t)
 {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t w = t / npad;
-    const int32_t i = (int32_t)(t % npad);
+    constexpr int V = VEC ? 4 : 1;
+    const int32_t q = npad / V;
+    const int64_t w = t / q;
+    const int32_t i0 = (int32_t)(t % q) * V;
     if (w >= words) return;
-    uint32_t v = 0;
-    if (i < N) {
-        const int64_t k0 = w * 32;
+    uint32_t out[V] = {};
+    const int64_t k0 = w * 32;
+    if (i0 < N && k0 < K) {
         const int rmax = K - k0 < 32 ? (int)(K - k0) : 32;
-        for (int r = 0; r < rmax; ++r) v |= (uint32_t)(X[(k0 + r) * ldx + i] != 0) << r;
+        const uint8_t* col = X + k0 * ldx + i0;
+        auto put = [&](uint32_t bytes, int r) {
+#pragma unroll
+            for (int v = 0; v < V; ++v) out[v] |= (uint32_t)((bytes >> (8 * v) & 0xFFu) != 0) << r;
+        };
+        // columns at or past N (inside the row's pitch, or past it when
+        // N = ldx) are masked below; a load never goes past the row
+        if (VEC && i0 + 4 > ldx) {
+            for (int r = 0; r < rmax; ++r) {
+                uint32_t b = 0;
+                for (int c = 0; c < 4 && i0 + c < ldx; ++c) b |= (uint32_t)col[r * ldx + c] << (8 * c);
+                put(b, r);
+            }
+        } else if (rmax == 32) {
+            uint32_t b[32];
+#pragma unroll
+            for (int r = 0; r < 32; ++r) {
+                if constexpr (VEC) b[r] = *reinterpret_cast<const uint32_t*>(col + r * ldx);
+                else b[r] = col[r * ldx];
+            }
+#pragma unroll
+            for (int r = 0; r < 32; ++r) put(b[r], r);
+        } else {
+            for (int r = 0; r < rmax; ++r) {
+                if constexpr (VEC) put(*reinterpret_cast<const uint32_t*>(col + r * ldx), r);
+                else put(col[r * ldx], r);
+            }
+        }
+#pragma unroll
+        for (int v = 1; v < V; ++v)
+            if (i0 + v >= N) out[v] = 0;
     }
-    Xb[w * npad + i] = v;
+    if constexpr (VEC) *reinterpret_cast<uint4*>(Xb + w * npad + i0) = make_uint4(out[0], out[1], out[2], out[3]);
+    else Xb[w * npad + i0] = out[0];
 }
 
-// The same packing four columns per thread: one 32-bit load per record
-// (rows 4-byte aligned: ldx % 4 == 0 and X aligned), npad % 4 == 0.
-__global__ void pack_bits4_kernel(const uint8_t* __restrict__ X, int64_t ldx, int64_t K, int32_t N, int32_t npad,
-                                  int64_t words, uint32_t* __restrict__ Xb)
+// Workgroups below `prep` form the digits of integer weights, the others pack.
+template <bool VEC>
+__global__ __launch_bounds__(256) void pack_kernel(const uint8_t* __restrict__ X, int64_t ldx, int64_t K, int32_t N,
+                                                   int32_t npad, int64_t words, uint32_t* __restrict__ Xb,
+                                                   const int64_t* __restrict__ m, uint8_t* __restrict__ digits,
+                                                   uint8_t* __restrict__ ndig, unsigned long long* __restrict__ psum,
+                                                   int32_t prep)
 {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int32_t q = npad / 4;
-    const int64_t w = t / q;
-    const int32_t i0 = (int32_t)(t % q) * 4;
-    if (w >= words) return;
-    uint32_t v0 = 0, v1 = 0, v2 = 0, v3 = 0;
-    if (i0 < N) {
-        const int64_t k0 = w * 32;
-        const int rmax = K - k0 < 32 ? (int)(K - k0) : 32;
-        // columns at or past N (inside the row's pitch, or past it when
-        // N = ldx) are masked below; a load never starts past the row
-        const bool full = i0 + 4 <= ldx;
-        for (int r = 0; r < rmax; ++r) {
-            const uint8_t* row = X + (k0 + r) * ldx;
-            uint32_t b;
-            if (full) {
-                b = *reinterpret_cast<const uint32_t*>(row + i0);
-            } else {
-                b = 0;
-                for (int c = 0; c < 4 && i0 + c < ldx; ++c) b |= (uint32_t)row[i0 + c] << (8 * c);
+    if ((int32_t)blockIdx.x < prep)
+        weight_digits(m, K, words / 2, digits, ndig, psum, (int)blockIdx.x, prep);
+    else
+        pack_columns<VEC>(X, ldx, K, N, npad, words, Xb, (int64_t)(blockIdx.x - prep) * 256 + threadIdx.x);
+}
+
+// Integer weights.  A workgroup of four waves forms one 64 x 64 tile (ti, tj)
+// of the upper triangle over a chunk of steps, each wave a quarter of them, as
+// 4 x 4 MFMA tiles of 16 x 16 (v_mfma_i32_16x16x64_i8); MFMA tile a, row r is
+// the tile's row 4 r + a, so that a lane's four columns are one 16-byte load.
+// Operand lane (l % 16, kg = l / 16) holds 16 records of a column: register j the bits 4 (kg % 2) +
+// j + 8 b, b < 4, of the column's word 2 step + kg / 2, as bytes (one shift
+// and one mask per four records).  B = x; A = x times the weights' digit: a
+// digit d < 128 under the mask 0x80 - x, which is 0x7F where x = 1 and keeps
+// nothing of d where x = 0.  The int32 sums are exact (127 per record); the
+// waves add theirs, times 128^digit, into the tile in LDS (FP64, exact
+// integers below 2^53), and the tile goes to part[chunk][tile].
+// Bound: VALU issue: a step of a wave is 130 VALU instructions (60 for A, 28
+// for B) and 16 MFMAs, 580 issue cycles against 256 of the matrix cores, two
+// waves to a SIMD.  N = 512, K = 131072, weights below 128: 31 us, and 42 with
+// weights up to some hundreds (a second pass over the steps that have them);
+// the bf16 product of the same weights took 150 us, with 277 VALU instructions
+// per 32 records and a load's latency in every step.  The whole call 218 -> 59
+// us; K = 32768, N = 20 (8 steps a workgroup instead of 16 a wave) 83 -> 30.
+constexpr int kLd = kTile + 2;  // LDS row of the tile: rows 4 apart on other banks
+
+__global__ __launch_bounds__(256, 2) void moments_i8_kernel(const uint32_t* __restrict__ Xb, int32_t npad, int64_t steps,
+                                                         int32_t N, const uint8_t* __restrict__ digits,
+                                                         const uint8_t* __restrict__ ndig, int64_t chunk_steps,
+                                                         int32_t tiles, double* __restrict__ part)
+{
+    __shared__ double tile[kTile * kLd];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int t = (int)(blockIdx.x % (unsigned)tiles);
+    const int64_t c = blockIdx.x / (unsigned)tiles;
+    int ti, tj;
+    upper_tile(t, (N + kTile - 1) / kTile, &ti, &tj);
+    const int i0 = ti * kTile, j0 = tj * kTile;
+    const int64_t s0 = c * chunk_steps;
+    const int64_t s1 = s0 + chunk_steps < steps ? s0 + chunk_steps : steps;
+    const int64_t quarter = (s1 - s0 + 3) / 4;
+    const int64_t w0 = s0 + wave * quarter < s1 ? s0 + wave * quarter : s1;
+    const int64_t w1 = w0 + quarter < s1 ? w0 + quarter : s1;
+    const int l16 = lane & 15, kg = lane >> 4;
+    const int sh = 4 * (kg & 1);
+    for (int e = threadIdx.x; e < kTile * kLd; e += 256) tile[e] = 0.0;
+    // digits of this wave's largest weight
+    int nd = 0;
+    for (int64_t s = w0 + lane; s < w1; s += 64) nd = max(nd, (int)ndig[s]);
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) nd = max(nd, __shfl_xor(nd, d, 64));
+    __syncthreads();
+
+    double scale = 1.0;
+    for (int p = 0; p < nd; ++p, scale *= 128.0) {
+        i32x4 acc[4][4];
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int b = 0; b < 4; ++b) acc[a][b] = (i32x4){0, 0, 0, 0};
+        // the steps of this pass, from s on
+        auto next = [&](int64_t s) {
+            if (p > 0)
+                while (s < w1 && ndig[s] <= p) ++s;
+            return s;
+        };
+        // three steps in flight: their words and digits come from L2 or beyond
+        uint4 ba[3], bb[3], wt[3];
+        int64_t at[3];
+        auto load = [&](int u, int64_t from) {
+            at[u] = next(from);
+            const int64_t s = at[u] < w1 ? at[u] : w0;  // (past the end: any step, its digits masked)
+            const uint32_t* row = Xb + (2 * s + (kg >> 1)) * npad + 4 * l16;
+            ba[u] = *reinterpret_cast<const uint4*>(row + i0);
+            bb[u] = *reinterpret_cast<const uint4*>(row + j0);
+            wt[u] = *reinterpret_cast<const uint4*>(digits + ((int64_t)p * steps + s) * 64 + kg * 16);
+        };
+        auto step = [&](int u, int last) {
+            constexpr uint32_t kOnes = 0x01010101u;
+            const uint32_t wa[4] = {ba[u].x, ba[u].y, ba[u].z, ba[u].w}, wb[4] = {bb[u].x, bb[u].y, bb[u].z, bb[u].w};
+            const uint32_t on = at[u] < w1 ? 0x7F7F7F7Fu : 0u;
+            const uint32_t dg[4] = {wt[u].x & on, wt[u].y & on, wt[u].z & on, wt[u].w & on};
+            i32x4 bop[4];
+            uint32_t xa[4];
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                const uint32_t x = wb[b] >> sh;
+                bop[b] = (i32x4){(int)(x & kOnes), (int)((x >> 1) & kOnes), (int)((x >> 2) & kOnes),
+                                 (int)((x >> 3) & kOnes)};
             }
-            v0 |= (uint32_t)((b & 0xFFu) != 0) << r;
-            v1 |= (uint32_t)((b & 0xFF00u) != 0) << r;
-            v2 |= (uint32_t)((b & 0xFF0000u) != 0) << r;
-            v3 |= (uint32_t)((b & 0xFF000000u) != 0) << r;
+#pragma unroll
+            for (int a = 0; a < 4; ++a) xa[a] = wa[a] >> sh;
+            load(u, at[last] + 1);
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                i32x4 aop;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) aop[j] = (int)(dg[j] & (0x80808080u - ((xa[a] >> j) & kOnes)));
+#pragma unroll
+                for (int b = 0; b < 4; ++b)
+                    acc[a][b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(aop, bop[b], acc[a][b], 0, 0, 0);
+            }
+        };
+        load(0, w0);
+        load(1, at[0] + 1);
+        load(2, at[1] + 1);
+        while (at[0] < w1) {
+            step(0, 2);
+            step(1, 0);
+            step(2, 1);
         }
-        if (i0 + 1 >= N) v1 = 0;
-        if (i0 + 2 >= N) v2 = 0;
-        if (i0 + 3 >= N) v3 = 0;
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (p == 0 || acc[a][b][e] != 0)
+                        atomicAdd(&tile[(a * 16 + kg * 4 + e) * kLd + b * 16 + l16], scale * (double)acc[a][b][e]);
     }
-    uint4 out = make_uint4(v0, v1, v2, v3);
-    *reinterpret_cast<uint4*>(Xb + w * npad + i0) = out;
+    __syncthreads();
+    double* dst = part + (c * tiles + t) * (int64_t)(kTile * kTile);
+    auto place = [](int i) { return (i & 3) * 16 + (i >> 2); };  // row or column i in the order of the MFMA tiles
+    for (int e = threadIdx.x; e < kTile * kTile; e += 256) dst[e] = tile[place(e / kTile) * kLd + place(e % kTile)];
+}
+
+// G[i][j] = f times the sum over chunks of the partial tiles (integer weights:
+// FP64, exact below 2^53), f = 1 or, scaled, -beta over the sum of the weights.
+// One thread per element of an upper-triangle tile; an off-diagonal tile's
+// element also gives G[j][i].  Every workgroup adds up the weight sums it
+// needs; the first writes the total to *sum.
+__global__ __launch_bounds__(256) void moments_int_reduce_kernel(const double* __restrict__ part, int64_t chunks,
+                                                                 int32_t tiles, int32_t N, double* __restrict__ G,
+                                                                 const unsigned long long* __restrict__ psum,
+                                                                 int32_t nsum, bool scaled, double beta,
+                                                                 double* __restrict__ sum)
+{
+    __shared__ unsigned long long red[4];
+    double f = 1.0;
+    if (scaled || blockIdx.x == 0) {
+        unsigned long long v = (int)threadIdx.x < nsum ? psum[threadIdx.x] : 0;
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+        __syncthreads();
+        const double total = (double)(red[0] + red[1] + red[2] + red[3]);
+        if (scaled) f = -beta / total;
+        if (blockIdx.x == 0 && threadIdx.x == 0) *sum = total;
+    }
+    const int t = (int)(blockIdx.x / (kTile * kTile / 256));
+    const int off = (int)(blockIdx.x % (kTile * kTile / 256)) * 256 + (int)threadIdx.x;
+    int ti, tj;
+    upper_tile(t, (N + kTile - 1) / kTile, &ti, &tj);
+    const int i = ti * kTile + off / kTile, j = tj * kTile + off % kTile;
+    if (i >= N || j >= N) return;
+    const double* src = part + (int64_t)t * (kTile * kTile) + off;
+    const int64_t stride = (int64_t)tiles * (kTile * kTile);
+    double s = 0.0;
+    int64_t c = 0;
+    for (; c + 8 <= chunks; c += 8) {
+        double v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = src[(c + u) * stride];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s += v[u];
+    }
+    for (; c < chunks; ++c) s += src[c * stride];
+    s *= f;
+    G[(int64_t)i * N + j] = s;
+    if (ti != tj) G[(int64_t)j * N + i] = s;
 }
 
 // 0xFFFF per set bit of a 2-bit field, in the matching half word.
@@ -246,14 +410,10 @@ __device__ __forceinline__ uint32_t half_mask(uint32_t two_bits)
 // records 8 (l / 16) .. + 7 of the 32-record step (the same assignment for A
 // and B, so their order inside the step does not matter); lane l receives C
 // rows 4 (l / 16) + e, column l % 16.  A = diag(piece_s(m)) x, B = x.
-// FP32 accumulation stays exact while flush * max(m) < 2^24: past that many
-// records the accumulators are added into G with FP64 atomics; the final
-// accumulators go to this wave's slot of `part` (FP32, exact integers).
+// FP32 accumulation; the accumulators go to this wave's slot of `part`.
 __global__ __launch_bounds__(256) void moments_kernel(const uint32_t* __restrict__ Xb, int32_t npad, int64_t words,
                                                       int32_t N, const uint16_t* __restrict__ pieces, int64_t kpad,
-                                                      int64_t chunk_words, int32_t tiles,
-                                                      const unsigned long long* __restrict__ max_m,
-                                                      float* __restrict__ part, double* __restrict__ G)
+                                                      int64_t chunk_words, int32_t tiles, float* __restrict__ part)
 {
     const int lane = threadIdx.x & 63;
     const int64_t gw = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
@@ -267,12 +427,6 @@ __global__ __launch_bounds__(256) void moments_kernel(const uint32_t* __restrict
     const int i0 = ti * kTile, j0 = tj * kTile;
     const int64_t w0 = c * chunk_words;
     const int64_t w1 = w0 + chunk_words < words ? w0 + chunk_words : words;
-    const unsigned long long mm = *max_m;
-    int64_t flush_words = w1 - w0;
-    if (mm > 0) {
-        const double lim = (double)(1 << 24) / ((double)mm * 1.01) / 32.0;
-        if (lim < (double)flush_words) flush_words = lim < 2.0 ? 2 : (int64_t)lim;
-    }
     const int l16 = lane & 15, lg = lane >> 4;
 
     f32x4 acc[4][4];
@@ -281,27 +435,7 @@ __global__ __launch_bounds__(256) void moments_kernel(const uint32_t* __restrict
 #pragma unroll
         for (int b = 0; b < 4; ++b) acc[a][b] = (f32x4){0.f, 0.f, 0.f, 0.f};
 
-    auto flush_atomic = [&]() {
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                const int j = j0 + b * 16 + l16;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int i = i0 + a * 16 + lg * 4 + e;
-                    const double v = (double)acc[a][b][e];
-                    if (i < N && j < N && v != 0.0) {
-                        atomicAdd(&G[(int64_t)i * N + j], v);
-                        if (ti != tj) atomicAdd(&G[(int64_t)j * N + i], v);
-                    }
-                }
-                acc[a][b] = (f32x4){0.f, 0.f, 0.f, 0.f};
-            }
-    };
-
     const int sh = lg * 8;
-    int64_t since = 0;
     for (int64_t w = w0; w < w1; ++w) {
         const uint32_t* row = Xb + w * npad;
         uint32_t ba[4], bb[4];
@@ -347,10 +481,6 @@ __global__ __launch_bounds__(256) void moments_kernel(const uint32_t* __restrict
                     acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aop, bop[b], acc[a][b], 0, 0, 0);
             }
         }
-        if (++since >= flush_words && w + 1 < w1) {
-            flush_atomic();
-            since = 0;
-        }
     }
     // this wave's partial tile: part[c][t][64][64]
     float* dst = part + (c * tiles + t) * (int64_t)(kTile * kTile);
@@ -382,9 +512,6 @@ __global__ void moments_reduce_kernel(const float* __restrict__ part, int64_t ch
     G[(int64_t)i * N + j] += s;
     if (ti != tj) G[(int64_t)j * N + i] += s;
 }
-
-// sum of the weights as FP64 into a device word.
-__global__ void moments_sum_kernel(const unsigned long long* sum_m, double* out) { *out = (double)*sum_m; }
 
 // ---- log Z by enumeration ----
 
@@ -513,15 +640,6 @@ __global__ __launch_bounds__(256) void logz_finish_kernel(const double* pm, cons
 
 }  // namespace
 
-hipError_t launch_moments_prep(const int64_t* m, int64_t K, int64_t kpad, uint16_t* pieces, unsigned long long* sum_m,
-                               unsigned long long* max_m, hipStream_t st)
-{
-    const int64_t n = kpad > K ? kpad : K;
-    const int64_t blocks = std::min<int64_t>(256, std::max<int64_t>(1, (n + 255) / 256));
-    hipLaunchKernelGGL(moments_prep_kernel, dim3((unsigned)blocks), dim3(256), 0, st, m, K, kpad, pieces, sum_m, max_m);
-    return hipGetLastError();
-}
-
 hipError_t launch_moments_prep_f64(const double* w, int64_t K, int64_t kpad, uint16_t* pieces, double* sum_w,
                                    unsigned long long* maxbits, hipStream_t st)
 {
@@ -556,31 +674,44 @@ hipError_t launch_moments_unscale(double* G, int64_t n, const unsigned long long
     return hipGetLastError();
 }
 
-hipError_t launch_pack_bits(const uint8_t* X, int64_t ldx, int64_t K, int32_t N, int32_t npad, int64_t words,
-                            uint32_t* Xb, hipStream_t st)
+namespace {
+
+// Packing, with `prep` workgroups forming the digits of integer weights m.
+hipError_t pack(const uint8_t* X, int64_t ldx, int64_t K, int32_t N, int32_t npad, int64_t words, uint32_t* Xb,
+                const int64_t* m, uint8_t* digits, uint8_t* ndig, unsigned long long* psum, int32_t prep,
+                hipStream_t st)
 {
-    if (ldx % 4 == 0 && (reinterpret_cast<uintptr_t>(X) & 3u) == 0 && npad % 4 == 0) {
-        const int64_t n = words * (npad / 4);
-        hipLaunchKernelGGL(pack_bits4_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, X, ldx, K, N, npad,
-                           words, Xb);
-    } else {
-        const int64_t n = words * npad;
-        hipLaunchKernelGGL(pack_bits_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, X, ldx, K, N, npad,
-                           words, Xb);
-    }
+    const bool vec = ldx % 4 == 0 && (reinterpret_cast<uintptr_t>(X) & 3u) == 0 && npad % 4 == 0;
+    const int64_t n = words * (vec ? npad / 4 : npad);
+    const dim3 grid((unsigned)((n + 255) / 256 + prep));
+    if (vec)
+        hipLaunchKernelGGL(pack_kernel<true>, grid, dim3(256), 0, st, X, ldx, K, N, npad, words, Xb, m, digits, ndig, psum,
+                           prep);
+    else
+        hipLaunchKernelGGL(pack_kernel<false>, grid, dim3(256), 0, st, X, ldx, K, N, npad, words, Xb, m, digits, ndig,
+                           psum, prep);
     return hipGetLastError();
 }
 
+int64_t align256(int64_t v) { return (v + 255) / 256 * 256; }
+
+}  // namespace
+
+hipError_t launch_pack_bits(const uint8_t* X, int64_t ldx, int64_t K, int32_t N, int32_t npad, int64_t words,
+                            uint32_t* Xb, hipStream_t st)
+{
+    return pack(X, ldx, K, N, npad, words, Xb, nullptr, nullptr, nullptr, nullptr, 0, st);
+}
+
 hipError_t launch_moments(const uint32_t* Xb, int32_t npad, int64_t words, int32_t N, const uint16_t* pieces,
-                          int64_t kpad, int64_t chunk_words, const unsigned long long* max_m, float* part, double* G,
-                          hipStream_t st)
+                          int64_t kpad, int64_t chunk_words, float* part, double* G, hipStream_t st)
 {
     const int nt = (N + kTile - 1) / kTile;
     const int32_t tiles = nt * (nt + 1) / 2;
     const int64_t chunks = (words + chunk_words - 1) / chunk_words;
     const int64_t waves = (int64_t)tiles * chunks;
     hipLaunchKernelGGL(moments_kernel, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, st, Xb, npad, words, N, pieces,
-                       kpad, chunk_words, tiles, max_m, part, G);
+                       kpad, chunk_words, tiles, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int64_t n = (int64_t)tiles * kTile * kTile;
@@ -589,9 +720,52 @@ hipError_t launch_moments(const uint32_t* Xb, int32_t npad, int64_t words, int32
     return hipGetLastError();
 }
 
-hipError_t launch_moments_sum(const unsigned long long* sum_m, double* out, hipStream_t st)
+MomentsWorkspace moments_int_workspace(int64_t K, int32_t N, int64_t limit)
 {
-    hipLaunchKernelGGL(moments_sum_kernel, dim3(1), dim3(1), 0, st, sum_m, out);
+    MomentsWorkspace w;
+    w.npad = (N + kTile - 1) / kTile * kTile;
+    w.steps = std::max<int64_t>(1, (K + 63) / 64);
+    const int64_t nt = w.npad / kTile;
+    w.tiles = nt * (nt + 1) / 2;
+    w.digits = align256(w.steps * 2 * w.npad * 4);
+    w.ndig = w.digits + align256(w.steps * 64 * kDigits);
+    w.psum = w.ndig + align256(w.steps);
+    w.part = w.psum + 257 * 8 + 248;
+    // At most 512 workgroups where the tiles allow it, two to a compute unit at
+    // once (N = 512, K = 131072: 504), of at least 8 steps.
+    const int64_t most_chunks = std::max<int64_t>(1, 512 / w.tiles);
+    w.chunk_steps = std::max<int64_t>(8, (w.steps + most_chunks - 1) / most_chunks);
+    // (a wave's int32 sums: 2^24 records of at most 127)
+    w.chunk_steps = std::min<int64_t>(w.chunk_steps, 1 << 20);
+    const int64_t tile_bytes = w.tiles * kTile * kTile * 8;
+    if (limit > 0) {
+        const int64_t most = std::max<int64_t>(1, (limit - w.part) / tile_bytes);
+        w.chunk_steps = std::max(w.chunk_steps, (w.steps + most - 1) / most);
+    }
+    w.bytes = w.part + (w.steps + w.chunk_steps - 1) / w.chunk_steps * tile_bytes;
+    return w;
+}
+
+hipError_t launch_moments_int(const uint8_t* X, int64_t ldx, const int64_t* m, int64_t K, int32_t N, double* G,
+                              double* sum, bool scaled, double beta, const MomentsWorkspace& w, void* ws,
+                              hipStream_t st)
+{
+    uint8_t* b = static_cast<uint8_t*>(ws);
+    uint32_t* Xb = reinterpret_cast<uint32_t*>(b);
+    uint8_t* digits = b + w.digits;
+    uint8_t* ndig = b + w.ndig;
+    unsigned long long* psum = reinterpret_cast<unsigned long long*>(b + w.psum);
+    double* part = reinterpret_cast<double*>(b + w.part);
+    const int64_t chunks = (w.steps + w.chunk_steps - 1) / w.chunk_steps;
+    const int32_t prep = (int32_t)std::min<int64_t>(256, (w.steps + 3) / 4);
+    hipError_t e = pack(X, ldx, K, N, w.npad, w.steps * 2, Xb, m, digits, ndig, psum, prep, st);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(moments_i8_kernel, dim3((unsigned)(w.tiles * chunks)), dim3(256), 0, st, Xb, w.npad, w.steps, N,
+                       digits, ndig, w.chunk_steps, (int32_t)w.tiles, part);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipLaunchKernelGGL(moments_int_reduce_kernel, dim3((unsigned)(w.tiles * (kTile * kTile / 256))), dim3(256), 0, st,
+                       part, chunks, (int32_t)w.tiles, N, G, psum, prep, scaled, beta,
+                       sum ? sum : reinterpret_cast<double*>(psum + 256));
     return hipGetLastError();
 }
 
@@ -623,11 +797,14 @@ hipError_t launch_logz(int32_t qtype, const void* Q, int32_t N, int32_t layout, 
 
 namespace {
 
-// Workspace of pns_moments_noalloc on each GPU: weight pieces, counters,
-// packed records and partial tiles of one call.  A device global holds no
-// valid address on the host: host code uses the per-device address from
-// hipGetSymbolAddress, never this name.
-constexpr size_t kScratchBytes = size_t(32) << 20;
+// Workspace of pns_moments_noalloc on each GPU: the workspace of one call of
+// the integer moments.  A device global holds no valid address on the host:
+// host code uses the per-device address from hipGetSymbolAddress, never this
+// name.  Calls of up to kCallBytes (packed records, 6 bytes of weights a
+// record and 16 KiB per 64 x 64 tile) are taken; what they need at most, with
+// 9 digit bytes a record and 32 KiB per tile, fits the array.
+constexpr size_t kCallBytes = size_t(32) << 20;
+constexpr size_t kScratchBytes = size_t(68) << 20;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 constexpr int kMaxDevices = 64;
@@ -678,7 +855,6 @@ extern "C" int pns_moments_noalloc(const uint8_t* X, int64_t ldx, const int64_t*
     if (ldx < N) return set_error(PNS_EINVAL, "ldx must be >= N");
     if (!on_device(X) || !on_device(m) || !on_device(G) || (sum_m && !on_device(sum_m)))
         return set_error(PNS_EINVAL, "X, m, G and sum_m must be device memory (nothing is staged here)");
-    // the sizes of pns_moments' workspace
     const int64_t kpad = std::max<int64_t>(64, (K + 63) / 64 * 64);
     const int32_t npad = (N + 63) / 64 * 64;
     const int64_t words = std::max<int64_t>(1, (K + 31) / 32);
@@ -686,35 +862,19 @@ extern "C" int pns_moments_noalloc(const uint8_t* X, int64_t ldx, const int64_t*
     const int64_t tiles = nt * (nt + 1) / 2;
     const size_t fixed = align256((size_t)3 * kpad * 2) + 256 + align256((size_t)words * npad * 4);
     const size_t tile_bytes = (size_t)tiles * 64 * 64 * 4;
-    if (fixed + tile_bytes > kScratchBytes)
+    if (fixed + tile_bytes > kCallBytes)
         return set_error(PNS_EINVAL,
                          "K = %lld records of N = %d need %zu bytes of workspace; the static workspace holds %zu "
                          "(use pns_moments)",
-                         (long long)K, N, fixed + tile_bytes, kScratchBytes);
-    // about 2048 waves, as pns_moments, with no more chunks than fit
-    int64_t chunk_words = std::max<int64_t>(32, (words * tiles + 2047) / 2048);
-    const int64_t max_chunks = (int64_t)((kScratchBytes - fixed) / tile_bytes);
-    if ((words + chunk_words - 1) / chunk_words > max_chunks) chunk_words = (words + max_chunks - 1) / max_chunks;
+                         (long long)K, N, fixed + tile_bytes, kCallBytes);
+    const MomentsWorkspace w = moments_int_workspace(K, N, (int64_t)kScratchBytes);
+    if (w.bytes > (int64_t)kScratchBytes)
+        return set_error(PNS_EINVAL, "K = %lld records of N = %d exceed the static workspace (use pns_moments)",
+                         (long long)K, N);
     void* base = nullptr;
     int rc = scratch_address(&base);
     if (rc) return rc;
-    unsigned char* b = static_cast<unsigned char*>(base);
-    uint16_t* pieces = reinterpret_cast<uint16_t*>(b);
-    b += align256((size_t)3 * kpad * 2);
-    unsigned long long* cnt = reinterpret_cast<unsigned long long*>(b);
-    b += 256;
-    uint32_t* Xb = reinterpret_cast<uint32_t*>(b);
-    b += align256((size_t)words * npad * 4);
-    float* part = reinterpret_cast<float*>(b);
-    hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    // every buffer is written before it is read, except the counters and G:
-    // cleared here (the workspace keeps the previous call's contents)
-    hipError_t e = launch_fill64(G, (int64_t)N * N, 0, st);
-    if (e == hipSuccess) e = launch_fill64(cnt, 3, 0, st);
-    if (e == hipSuccess) e = launch_moments_prep(m, K, kpad, pieces, cnt, cnt + 1, st);
-    if (e == hipSuccess) e = launch_pack_bits(X, ldx, K, N, npad, words, Xb, st);
-    if (e == hipSuccess) e = launch_moments(Xb, npad, words, N, pieces, kpad, chunk_words, cnt + 1, part, G, st);
-    if (e == hipSuccess && sum_m) e = launch_moments_sum(cnt, sum_m, st);
+    hipError_t e = launch_moments_int(X, ldx, m, K, N, G, sum_m, false, 0.0, w, base, reinterpret_cast<hipStream_t>(stream));
     if (e != hipSuccess) return set_error(PNS_EDEVICE, "moments kernels: %s", hipGetErrorString(e));
     return PNS_OK;
 }

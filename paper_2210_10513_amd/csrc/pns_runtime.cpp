@@ -1855,67 +1855,67 @@ namespace {
 
 // G (N x N, FP64, overwritten) = X^T diag(w) X, queued on `st` without a
 // host synchronisation; device pointers.  The weights are integers m (exact
-// path) or, when m is NULL, FP64 weights wf.  The sum of the weights goes to
-// *sum_host (synchronising) and/or *sum_dev (queued), either may be NULL.
-// Workspace comes from the stream-ordered allocator and is released in
-// stream order.
+// path) or, when m is NULL, FP64 weights wf.  With `scaled`, G is multiplied
+// by -beta over the sum of the weights (sum_dev then required for FP64
+// weights).  The sum of the weights goes to *sum_host (synchronising) and/or
+// *sum_dev (queued), either may be NULL.  Workspace comes from the
+// stream-ordered allocator and is released in stream order.
 int moments_device(const uint8_t* X, int64_t ldx, const int64_t* m, const double* wf, int64_t K, int32_t N, double* G,
-                   hipStream_t st, double* sum_host, double* sum_dev)
+                   hipStream_t st, double* sum_host, double* sum_dev, bool scaled = false, double beta = 0.0)
 {
-    const int64_t kpad = std::max<int64_t>(64, round_up(K, 64));
-    const int32_t npad = (int32_t)round_up(N, 64);
-    const int64_t words = std::max<int64_t>(1, (K + 31) / 32);
-    const int nt = npad / 64;
-    const int64_t tiles = (int64_t)nt * (nt + 1) / 2;
-    // words per wave: at least 32 (1024 records), about 2048 waves in all
-    const int64_t chunk_words = std::max<int64_t>(32, (words * tiles + 2047) / 2048);
-    const int64_t chunks = (words + chunk_words - 1) / chunk_words;
-    uint16_t* pieces = nullptr;
-    unsigned long long* cnt = nullptr;
-    uint32_t* Xb = nullptr;
-    float* part = nullptr;
-    auto release = [&]() {
-        if (pieces) (void)hipFreeAsync(pieces, st);
-        if (cnt) (void)hipFreeAsync(cnt, st);
-        if (Xb) (void)hipFreeAsync(Xb, st);
-        if (part) (void)hipFreeAsync(part, st);
-    };
-    hipError_t e = hipMallocAsync(reinterpret_cast<void**>(&pieces), (size_t)3 * kpad * sizeof(uint16_t), st);
-    // cnt: [0] sum of the weights (uint64, or FP64 bits), [1] largest integer
-    // weight (0 on the FP64 path: no flushes), [2] largest |FP64 weight| bits
-    if (e == hipSuccess) e = hipMallocAsync(reinterpret_cast<void**>(&cnt), 3 * sizeof(unsigned long long), st);
-    if (e == hipSuccess) e = hipMallocAsync(reinterpret_cast<void**>(&Xb), (size_t)words * npad * sizeof(uint32_t), st);
-    if (e == hipSuccess)
-        e = hipMallocAsync(reinterpret_cast<void**>(&part), (size_t)chunks * tiles * 64 * 64 * sizeof(float), st);
-    if (e != hipSuccess) {
+    uint8_t* ws = nullptr;
+    const double* sum_at = nullptr;  // the sum of the weights on the device
+    hipError_t e = hipSuccess;
+    auto allocate = [&](int64_t bytes) { return hipMallocAsync(reinterpret_cast<void**>(&ws), (size_t)bytes, st); };
+    if (m) {
+        const MomentsWorkspace w = moments_int_workspace(K, N, 0);
+        if ((e = allocate(w.bytes)) == hipSuccess) {
+            double* sum = sum_dev ? sum_dev : reinterpret_cast<double*>(ws + w.psum) + 256;
+            sum_at = sum;
+            e = launch_moments_int(X, ldx, m, K, N, G, sum, scaled, beta, w, ws, st);
+        }
+    } else {
+        const int64_t kpad = std::max<int64_t>(64, round_up(K, 64));
+        const int32_t npad = (int32_t)round_up(N, 64);
+        const int64_t words = std::max<int64_t>(1, (K + 31) / 32);
+        const int nt = npad / 64;
+        const int64_t tiles = (int64_t)nt * (nt + 1) / 2;
+        // words per wave: at least 32 (1024 records), about 2048 waves in all
+        const int64_t chunk_words = std::max<int64_t>(32, (words * tiles + 2047) / 2048);
+        const int64_t chunks = (words + chunk_words - 1) / chunk_words;
+        // [sum of the weights, largest |weight| bits | pieces | packed records | partial tiles]
+        const int64_t at_pieces = 256, at_words = at_pieces + round_up(3 * kpad * 2, 256);
+        const int64_t at_part = at_words + round_up(words * npad * 4, 256);
+        if ((e = allocate(at_part + chunks * tiles * 64 * 64 * 4)) == hipSuccess) {
+            double* sum = reinterpret_cast<double*>(ws);
+            unsigned long long* maxbits = reinterpret_cast<unsigned long long*>(ws) + 1;
+            uint16_t* pieces = reinterpret_cast<uint16_t*>(ws + at_pieces);
+            uint32_t* Xb = reinterpret_cast<uint32_t*>(ws + at_words);
+            sum_at = sum;
+            e = launch_fill64(G, (int64_t)N * N, 0, st);
+            if (e == hipSuccess) e = launch_fill64(sum, 2, 0, st);
+            if (e == hipSuccess) e = launch_moments_prep_f64(wf, K, kpad, pieces, sum, maxbits, st);
+            if (e == hipSuccess) e = launch_pack_bits(X, ldx, K, N, npad, words, Xb, st);
+            if (e == hipSuccess)
+                e = launch_moments(Xb, npad, words, N, pieces, kpad, chunk_words, reinterpret_cast<float*>(ws + at_part), G,
+                                   st);
+            if (e == hipSuccess) e = launch_moments_unscale(G, (int64_t)N * N, maxbits, st);
+            if (e == hipSuccess && sum_dev) e = hipMemcpyAsync(sum_dev, sum, sizeof(double), hipMemcpyDeviceToDevice, st);
+            if (e == hipSuccess && scaled) e = launch_moments_to_grad(G, (int64_t)N * N, beta, sum_dev, st);
+        }
+    }
+    if (!ws) {
         (void)hipGetLastError();
-        release();
         return fail(PNS_ENOMEM, "workspace allocation failed: %s", hipGetErrorString(e));
     }
-    e = launch_fill64(G, (int64_t)N * N, 0, st);
-    if (e == hipSuccess) e = launch_fill64(cnt, 3, 0, st);
-    if (e == hipSuccess) {
-        if (m) e = launch_moments_prep(m, K, kpad, pieces, cnt, cnt + 1, st);
-        else e = launch_moments_prep_f64(wf, K, kpad, pieces, reinterpret_cast<double*>(cnt), cnt + 2, st);
-    }
-    if (e == hipSuccess) e = launch_pack_bits(X, ldx, K, N, npad, words, Xb, st);
-    if (e == hipSuccess) e = launch_moments(Xb, npad, words, N, pieces, kpad, chunk_words, cnt + 1, part, G, st);
-    if (e == hipSuccess && !m) e = launch_moments_unscale(G, (int64_t)N * N, cnt + 2, st);
-    if (e == hipSuccess && sum_dev) {
-        if (m) e = launch_moments_sum(cnt, sum_dev, st);
-        else e = hipMemcpyAsync(sum_dev, cnt, sizeof(double), hipMemcpyDeviceToDevice, st);
-    }
-    unsigned long long hs = 0;
+    double hs = 0.0;
     if (e == hipSuccess && sum_host) {
-        e = hipMemcpyAsync(&hs, cnt, sizeof(hs), hipMemcpyDeviceToHost, st);
+        e = hipMemcpyAsync(&hs, sum_at, sizeof(hs), hipMemcpyDeviceToHost, st);
         if (e == hipSuccess) e = hipStreamSynchronize(st);
     }
-    release();
+    (void)hipFreeAsync(ws, st);
     if (e != hipSuccess) return hip_fail(e, "moments kernels");
-    if (sum_host) {
-        if (m) *sum_host = (double)hs;
-        else std::memcpy(sum_host, &hs, sizeof(double));
-    }
+    if (sum_host) *sum_host = hs;
     return PNS_OK;
 }
 
@@ -1969,8 +1969,10 @@ int moments_entry(const uint8_t* X, int64_t ldx, const int64_t* m, const double*
 }
 
 // Snapshot moments of one problem with multiplicities (rb = false) or
-// expected multiplicities (rb = true) as weights.
-int snapshot_moments(pns_ctx* ctx, int32_t problem, bool rb, double* G, double* sum_w)
+// expected multiplicities (rb = true) as weights; scaled: times -beta over
+// their sum (sum_w on the device).
+int snapshot_moments(pns_ctx* ctx, int32_t problem, bool rb, double* G, double* sum_w, bool scaled = false,
+                     double beta = 0.0)
 {
     g_error.clear();
     if (!ctx || !G) return fail(PNS_EINVAL, "NULL argument");
@@ -1986,7 +1988,7 @@ int snapshot_moments(pns_ctx* ctx, int32_t problem, bool rb, double* G, double* 
     const bool sd = sum_w && is_device_ptr(sum_w);
     rc = moments_device(ctx->snap_x + row0 * ctx->max_pitch, ctx->max_pitch, rb ? nullptr : ctx->snap_M + row0,
                         rb ? ctx->snap_w + row0 : nullptr, K, R.N, dG, ctx->stream, sum_w && !sd ? sum_w : nullptr,
-                        sd ? sum_w : nullptr);
+                        sd ? sum_w : nullptr, scaled, beta);
     if (!rc && !gd) {
         hipError_t e = hipMemcpyAsync(G, dG, (size_t)R.N * R.N * 8, hipMemcpyDeviceToHost, ctx->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
@@ -2036,11 +2038,7 @@ int pns_logz_grad(pns_ctx* ctx, int32_t problem, double beta, int32_t rb, double
     if (!ctx || !grad || !sum_w) return fail(PNS_EINVAL, "NULL argument");
     if (!is_device_ptr(grad) || !is_device_ptr(sum_w)) return fail(PNS_EINVAL, "grad and sum_w must be device memory");
     if (!std::isfinite(beta)) return fail(PNS_EINVAL, "beta must be finite");
-    int rc = snapshot_moments(ctx, problem, rb != 0, grad, sum_w);
-    if (rc) return rc;
-    const int64_t N = ctx->probs[problem].N;
-    HIP_TRY(launch_moments_to_grad(grad, N * N, beta, sum_w, ctx->stream), "gradient");
-    return PNS_OK;
+    return snapshot_moments(ctx, problem, rb != 0, grad, sum_w, true, beta);
 }
 
 int pns_read_rb_weights(pns_ctx* ctx, double* log_w, double* snap_w, double* hist_rb)

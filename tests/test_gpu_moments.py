@@ -47,6 +47,31 @@ def test_moments_large_weights_within_stated_bound():
     assert rel.max() <= 64 * 2.0 ** -24 + 2.0 ** -24
 
 
+@pytest.mark.parametrize("K,N", [(64, 3), (200, 65), (4097, 40)])
+def test_moments_digits_of_the_weights(K, N):
+    """Weights around the powers of 128 that set their number of digits, steps
+    of 64 records with few and with many digits, zero and negative weights:
+    exact while the entries stay below 2^53; INT64_MAX (a saturated
+    multiplicity) to the rounding of the additions (one per partial sum)."""
+    from paper_2210_10513_amd import binding
+    rng = np.random.default_rng(K)
+    X = (rng.random((K, N)) < 0.5).astype(np.uint8) * np.uint8(7)  # any nonzero byte is a set bit
+    m = rng.integers(0, 128, size=K).astype(np.int64)
+    for e in range(1, 6):
+        at = rng.choice(K, size=5, replace=False)
+        m[at] = np.array([128 ** e - 1, 128 ** e, 128 ** e + 1, -5, 0])
+    G = np.zeros((N, N))
+    sm = binding.pns_moments(X, m, G)
+    mp = np.maximum(m, 0)
+    want = ((X != 0).astype(np.int64).T * mp) @ (X != 0).astype(np.int64)
+    assert sm == float(mp.sum()) and np.array_equal(G, want.astype(np.float64))
+    m[3] = np.iinfo(np.int64).max
+    X[3] = 1
+    binding.pns_moments(X, m, G)
+    wantf = want.astype(np.float64) - float(mp[3]) * np.outer(X[3] != 0, X[3] != 0) + 2.0 ** 63
+    assert np.abs(G / wantf - 1.0).max() < 1e-12
+
+
 def test_moments_device_buffers_and_ldx():
     import torch
     from paper_2210_10513_amd import binding
