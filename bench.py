@@ -147,6 +147,8 @@ def _kernel_name(c) -> str:
     block, groups = (int(v) for v in c["tile"].split("x"))
     if c["flavour"] == 5:
         return f"wave_kernel<short, {block // 64}, {groups}, false>"
+    if c["flavour"] in (6, 7):
+        return f"full_kernel<short, int, {block // 64}, {groups}, {'true' if c['flavour'] == 7 else 'false'}, false>"
     return f"step_kernel<short, int, {block}, {groups}, {c['flavour']}, false>"
 
 

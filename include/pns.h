@@ -104,7 +104,10 @@ typedef struct pns_opts {
     int32_t chunk;          /* steps per launch in PERSISTENT / GRAPH; 0 = all
                                steps of a pns_run in one launch                   */
     int32_t block;          /* threads per workgroup (one workgroup per chain);
-                               0 = chosen from the tuned table.  Step-kernel
+                               0 = chosen from the tuned table (all-bits and
+                               drawn-subset problems then run a kernel and
+                               workgroup of the library's choice, with the same
+                               records; pns_class_profile names it).  Step-kernel
                                tiles (block x groups): 64x1, 64x2, 64x4, 128x1,
                                128x2, 128x4, 256x1, 256x2, 256x4, 256x8, 512x2,
                                512x4, 1024x2, 1024x4, and 256x16 for 32-bit fields
@@ -148,7 +151,8 @@ typedef struct pns_problem {
     double beta;            /* used when betas is NULL                           */
 } pns_problem;
 
-/* Tile and subset size of one problem as the library runs it. */
+/* Tile and subset size of one problem as chosen or asked for (the kernel and
+ * workgroup that run it where no tile was asked for: pns_class_profile). */
 typedef struct pns_problem_info {
     int32_t N;
     int32_t subset_size;
@@ -456,7 +460,9 @@ int pns_refresh(pns_ctx* ctx);
  * previous run's events (one host synchronisation per run). */
 typedef struct pns_class_profile {
     int32_t block, groups;  /* tile of the class                               */
-    int32_t flavour;        /* as pns_problem_info.flavour                     */
+    int32_t flavour;        /* as pns_problem_info.flavour; 6, 7: the kernel of
+                               all-bits and of drawn-subset problems whose tile
+                               was left open                                   */
     int32_t chains;         /* chains of the class                             */
     int32_t N_min, N_max;   /* smallest and largest problem of the class       */
     int64_t launches;       /* kernel launches timed                           */

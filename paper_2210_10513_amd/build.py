@@ -21,16 +21,20 @@ LIB = os.path.join(LIBDIR, "libpns.so")
 ARCH = os.environ.get("PNS_OFFLOAD_ARCH", "gfx950")
 
 SOURCES = ["pns_step_i16.hip", "pns_step_i32.hip", "pns_step_i64.hip", "pns_step_f32.hip", "pns_wave_i16.hip",
-           "pns_wave_i32.hip", "pns_kernels.hip", "pns_fields.hip", "pns_moments.hip", "pns_cont.hip", "pns_runtime.cpp"]
+           "pns_wave_i32.hip", "pns_full_i16.hip", "pns_full_i32.hip", "pns_full_i64.hip", "pns_full_f32.hip",
+           "pns_kernels.hip", "pns_fields.hip", "pns_moments.hip", "pns_cont.hip", "pns_runtime.cpp"]
 
 # Per-source additions: the moment kernel adds FP64 partial sums with the
-# hardware atomic add (device memory only); the window kernels and the
-# continuous sampler keep the constants of their rare paths where they are used instead of in registers
-# across the step loop (machine loop-invariant code motion off).
+# hardware atomic add (device memory only); the window kernels, the kernels of
+# all bits and drawn subsets and the continuous sampler keep the constants of
+# their rare paths where they are used instead of in registers across the step
+# loop (machine loop-invariant code motion off).
+NO_LICM = ["-mllvm", "-disable-machine-licm"]
 EXTRA_FLAGS = {"pns_moments.hip": ["-munsafe-fp-atomics"],
-               "pns_cont.hip": ["-mllvm", "-disable-machine-licm"],
-               "pns_wave_i16.hip": ["-mllvm", "-disable-machine-licm"],
-               "pns_wave_i32.hip": ["-mllvm", "-disable-machine-licm"]}
+               "pns_cont.hip": NO_LICM,
+               "pns_wave_i16.hip": NO_LICM,
+               "pns_wave_i32.hip": NO_LICM,
+               **{f"pns_full_{t}.hip": NO_LICM for t in ("i16", "i32", "i64", "f32")}}
 
 HIPCC_FLAGS = [
     f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC",

@@ -1,0 +1,14 @@
+// Step kernels over all bits and drawn subsets, one to eight waves per chain,
+// for int16_t coefficients with int32_t fields.
+#include "pns_full.h"
+
+namespace pns {
+
+hipError_t launch_full_i16(bool drawn, bool instr, int block, int groups, int grid, size_t dyn, hipStream_t st,
+                           const StepArgs& a)
+{
+    PNS_FULL_TILE_LIST(PNS_FULL_DISPATCH_TILE, int16_t, int32_t)
+    return hipErrorInvalidConfiguration;
+}
+
+}  // namespace pns

@@ -27,6 +27,11 @@ struct Problem {
     int32_t qtype;     // QType
 };
 
+// Flavour codes of the launch classes, next to the step kernel's 0 .. 4 and
+// the window kernel's 5: the one-to-eight-wave kernel over all bits or a drawn
+// subset (pns_full.h).
+constexpr int32_t kFlavFull = 6, kFlavDraw = 7;
+
 // Everything a step kernel launch needs.  Chain c of the context stores its
 // state at field offset foff[c] (fields x, h, rand-set membership) and at
 // index c in the per-chain arrays.
@@ -110,6 +115,14 @@ hipError_t launch_fields(int32_t qtype, int32_t htype, int64_t pitch, const Init
 // the tile exists.  dyn_lds is the dynamic LDS byte count (random subsets).
 hipError_t launch_steps(int32_t qtype, int32_t htype, int32_t flav, bool instr, int32_t block, int32_t groups,
                         int32_t grid, size_t dyn_lds, hipStream_t stream, const StepArgs& args);
+hipError_t launch_full_i16(bool drawn, bool instr, int block, int groups, int grid, size_t dyn, hipStream_t st,
+                           const StepArgs& a);
+hipError_t launch_full_i32(bool drawn, bool instr, int block, int groups, int grid, size_t dyn, hipStream_t st,
+                           const StepArgs& a);
+hipError_t launch_full_i64(bool drawn, bool instr, int block, int groups, int grid, size_t dyn, hipStream_t st,
+                           const StepArgs& a);
+hipError_t launch_full_f32(bool drawn, bool instr, int block, int groups, int grid, size_t dyn, hipStream_t st,
+                           const StepArgs& a);
 hipError_t launch_steps_i16(int flav, bool instr, int block, int groups, int grid, size_t dyn, hipStream_t st,
                             const StepArgs& a, bool probe);
 hipError_t launch_steps_i32(int flav, bool instr, int block, int groups, int grid, size_t dyn, hipStream_t st,

@@ -317,6 +317,14 @@ __global__ void fill64_kernel(int64_t* p, int64_t count, int64_t value)
 hipError_t launch_steps(int32_t qtype, int32_t htype, int32_t flav, bool instr, int32_t block, int32_t groups,
                         int32_t grid, size_t dyn_lds, hipStream_t stream, const StepArgs& args)
 {
+    if (flav == kFlavFull || flav == kFlavDraw) {
+        const bool drawn = flav == kFlavDraw;
+        if (qtype == Q_I16 && htype == H_I32) return launch_full_i16(drawn, instr, block, groups, grid, dyn_lds, stream, args);
+        if (qtype == Q_I32 && htype == H_I32) return launch_full_i32(drawn, instr, block, groups, grid, dyn_lds, stream, args);
+        if (qtype == Q_I32 && htype == H_I64) return launch_full_i64(drawn, instr, block, groups, grid, dyn_lds, stream, args);
+        if (qtype == Q_F32 && htype == H_F64) return launch_full_f32(drawn, instr, block, groups, grid, dyn_lds, stream, args);
+        return hipErrorInvalidConfiguration;
+    }
     if (flav == 5) {
         if (qtype == Q_I16 && htype == H_I32) return launch_waves_i16(instr, block, groups, grid, stream, args, false);
         if (qtype == Q_I32 && htype == H_I32) return launch_waves_i32(instr, block, groups, grid, stream, args, false);

@@ -286,6 +286,57 @@ Tile default_tile_for(int32_t mode, int32_t N, int32_t n, int32_t qtype, int32_t
     return t;
 }
 
+// The kernel that runs a problem whose tile the caller did not ask for: its
+// workgroup shape and flavour.  Where the step kernel would weigh every bit or
+// a drawn subset, the kernel of pns_full.h does (equal records), on the tile
+// that measured fastest (us per step, RF / Basic n = N/16, +-100 weights):
+//   * int32 fields: one wave of 4, 8, 12 or 16 bits per lane up to 1024 bits,
+//     then four and eight waves of as few groups as hold N.  4096 chains of
+//     N = 1000: 4.3 / 6.9 (one wave), 5.5 / 9.1 (four waves of one group);
+//     1024 chains of N = 3000: 3.2 / 4.7 (256 x 3), 4.6 / 6.3 (256 x 4).
+//   * up to two chains per CU a step's latency counts and more waves of fewer
+//     groups win: 256 chains of N = 1000 1.14 (256 x 1), 1.49 (64 x 4); of
+//     N = 2000 1.34 (512 x 1), 1.45 (256 x 2).
+//   * floats weigh with the exponential itself: one group per lane up to two
+//     chains per CU, and at all counts for N > 768 without a drawn subset
+//     (1024 chains of N = 1000: 2.3, one wave 2.6, the step kernel 2.4).
+// The step kernel stays where it is the faster one: int64 fields up to 1024
+// bits (256 chains of N = 1000: 1.9 against 2.3) and random sets of int64
+// fields (2.2 against 2.8), random sets of floats above 512 up to 1024 bits
+// (1024 chains of N = 1000: 2.7 against 3.3), and drawn subsets of floats above
+// 8192 bits, whose 32 fields per lane spill registers (12.5 against 13.4).
+struct Exec {
+    Tile tile;
+    int32_t flav;
+};
+
+Exec exec_of(Tile tile, int32_t flav, bool asked, int32_t N, int32_t htype, bool random_sets, int64_t chains)
+{
+    if (asked || (flav != 0 && flav != 2)) return {tile, flav};
+    const bool drawn = flav == 2, few = chains <= 512;
+    const bool f64 = htype == H_F64, i64 = htype == H_I64;
+    if (i64 && (drawn ? random_sets : N <= 1024)) return {tile, flav};
+    if (f64 && drawn && (N > 8192 || (random_sets && N > 512 && N <= 1024))) return {tile, flav};
+    Tile t{512, 8};
+    if (N <= 256) t = {64, 1};
+    else if (N <= 512) t = i64 || (f64 && few) ? Tile{128, 1} : Tile{64, 2};
+    else if (N <= 1024) t = few || i64 || (f64 && !drawn && N > 768) ? Tile{256, 1} : N <= 768 ? Tile{64, 3} : Tile{64, 4};
+    else if (N <= 2048) t = few ? Tile{512, 1} : Tile{256, 2};
+    else if (N <= 3072) t = i64 ? Tile{512, 2} : Tile{256, 3};
+    else if (N <= 4096) t = few || i64 || !drawn ? Tile{512, 2} : Tile{256, 4};
+    else if (N <= 6144) t = {512, 3};
+    else if (N <= 8192) t = {512, 4};
+    return {t, drawn ? kFlavDraw : kFlavFull};
+}
+
+// Dynamic LDS of a launch: the step kernel's diagonal, after the table of a
+// drawn subset; that table for the drawn subsets of pns_full.h; nothing else.
+size_t dyn_lds(int32_t flav, int64_t pitch)
+{
+    if (flav == 5 || flav == kFlavFull) return 0;
+    return (size_t)pitch * 4 * (flav == 2 ? 2 : 1);
+}
+
 // A problem's matrix as the kernels read it, prepared on the host.
 struct Prepared {
     std::vector<uint8_t> A, D;  // A: N x pitch, zero diagonal; D: diagonal [pitch]
@@ -405,7 +456,8 @@ struct ProblemSpec {
     int32_t N = 0, layout = 0, n = 0, chains = 0;
     int64_t L0 = 100;
     std::vector<double> betas;
-    Tile tile{0, 0};  // 0: default table
+    Tile tile{0, 0};     // 0: default table
+    bool asked = false;  // the caller asked for this tile
 };
 
 struct ProblemRun {
@@ -413,6 +465,8 @@ struct ProblemRun {
     int64_t pitch, L0, num_sets;
     int32_t chain_begin, chains;
     Tile tile;
+    bool asked;  // the caller asked for the tile
+    Exec exec;   // what runs
     void* A = nullptr;
     void* diag = nullptr;
     void* A2 = nullptr;     // staging copies for pns_set_q (allocated on first use)
@@ -853,6 +907,8 @@ int create_impl(pns_ctx** out, std::vector<ProblemSpec>& specs, int32_t mode, co
         R.chains = S.chains;
         R.tile = S.tile;
         R.flav = flav[p];
+        R.asked = S.asked;
+        R.exec = exec_of(S.tile, flav[p], S.asked, S.N, htype, mode == PNS_MODE_UNBIASED_RAND, total_chains);
         ctx->probs.push_back(R);
         ProblemRun& RR = ctx->probs.back();
         int r = dev_alloc(reinterpret_cast<uint8_t**>(&RR.A), pp[p]->A.size() + kRowTailBytes);
@@ -877,19 +933,17 @@ int create_impl(pns_ctx** out, std::vector<ProblemSpec>& specs, int32_t mode, co
         D.s = RR.s;
         D.qtype = qtype;
         ctx->max_pitch = std::max(ctx->max_pitch, RR.pitch);
-        const auto key = std::make_pair(std::make_pair(RR.tile.block, RR.tile.groups), RR.flav);
+        const auto key = std::make_pair(std::make_pair(RR.exec.tile.block, RR.exec.tile.groups), RR.exec.flav);
         if (!class_of.count(key)) {
             class_of[key] = ctx->classes.size();
             LaunchClass k;
-            k.tile = RR.tile;
-            k.flav = RR.flav;
+            k.tile = RR.exec.tile;
+            k.flav = RR.exec.flav;
             k.dyn = 0;
             ctx->classes.push_back(k);
         }
         LaunchClass& K = ctx->classes[class_of[key]];
-        // dynamic LDS: the diagonal, after the random-subset table for drawn
-        // subsets (the window kernel keeps neither)
-        K.dyn = std::max(K.dyn, RR.flav == 5 ? (size_t)0 : (size_t)RR.pitch * 4 * (RR.flav == 2 ? 2 : 1));
+        K.dyn = std::max(K.dyn, dyn_lds(RR.exec.flav, RR.pitch));
         for (int32_t c = 0; c < S.chains; ++c) {
             ctx->h_chain_problem[c0 + c] = (int32_t)p;
             ctx->h_foff[c0 + c] = f0 + (int64_t)c * RR.pitch;
@@ -898,7 +952,7 @@ int create_impl(pns_ctx** out, std::vector<ProblemSpec>& specs, int32_t mode, co
             K.chains.push_back(c0 + c);
         }
         // a step costs about the lane work of the tile: block * groups
-        K.cost += (double)S.chains * RR.tile.block * RR.tile.groups;
+        K.cost += (double)S.chains * RR.exec.tile.block * RR.exec.tile.groups;
         f0 += (int64_t)S.chains * RR.pitch;
         c0 += S.chains;
     }
@@ -1125,10 +1179,11 @@ int reconfigure(pns_ctx* ctx, Tile t, int32_t n)
     D.s = R.s;
     D.qtype = ctx->qtype;
     HIP_TRY(hipMemcpy(ctx->problems, &D, sizeof(Problem), hipMemcpyHostToDevice), "reconfigure");
+    R.exec = exec_of(t, R.flav, false, R.N, ctx->htype, ctx->mode == PNS_MODE_UNBIASED_RAND, ctx->num_chains);
     LaunchClass& K = ctx->classes[0];
-    K.tile = t;
-    K.flav = R.flav;
-    K.dyn = R.flav == 5 ? 0 : (size_t)R.pitch * 4 * (R.flav == 2 ? 2 : 1);
+    K.tile = R.exec.tile;
+    K.flav = R.exec.flav;
+    K.dyn = dyn_lds(K.flav, R.pitch);
     return reset_zero_state(ctx);
 }
 
@@ -1250,6 +1305,9 @@ int autotune_impl(const ProblemSpec& base, int32_t mode, const pns_opts& o, int3
         if (window_cap && (int64_t)tl.block * 4 * tl.groups != window_cap) continue;
         for (int32_t n : ns) {
             const int32_t fl = flavour_for(mode, base.N, n, tl, ctx->qtype, ctx->htype);
+            // (every table tile of these runs the same kernel, see exec_of)
+            const Tile def = default_tile(base.N);
+            if ((fl == 0 || fl == 2) && (tl.block != def.block || tl.groups != def.groups)) continue;
             if (fl < 0 || (wide_tile(tl) && fl != 3 && fl != 4 && fl != 5)) continue;
             if (window_cap && fl != 5) continue;
             double r = 0.0, fr = 0.0;
@@ -1347,6 +1405,7 @@ int pns_create(pns_ctx** out, const void* Q, int32_t N, double beta, int32_t sub
         if (!(b >= 0.0) || !std::isfinite(b)) return fail(PNS_EINVAL, "beta must be finite and >= 0");
     if (o.block > 0 || o.groups > 0) {
         const Tile def = default_tile(N);
+        S.asked = true;
         S.tile.block = o.block > 0 ? o.block : def.block;
         S.tile.groups = o.groups > 0 ? o.groups
                                      : std::max<int32_t>(1, (int32_t)((N + S.tile.block * 4 - 1) / (S.tile.block * 4)));
@@ -1410,7 +1469,7 @@ int pns_create_batch(pns_ctx** out, int32_t num_problems, const pns_problem* pro
             if (!(b >= 0.0) || !std::isfinite(b)) return fail(PNS_EINVAL, "problem %d: beta must be finite and >= 0", p);
         tune[p] = o.autotune || tune_n[p];
         if (!tune[p] && o.block > 0 && (int64_t)o.block * 4 * std::max(1, o.groups) >= q.N)
-            S.tile = {o.block, std::max(1, o.groups)};
+            S.tile = {o.block, std::max(1, o.groups)}, S.asked = true;
     }
     // every matrix is prepared once, for the trials and the context
     std::vector<Prepared> preps((size_t)num_problems);
@@ -2241,18 +2300,20 @@ int pns_optimize(pns_ctx* ctx, int64_t steps, double temperature)
         for (size_t p = 0; p < ctx->probs.size(); ++p) {
             const ProblemRun& R = ctx->probs[p];
             const int32_t flav = (ctx->mode != PNS_MODE_RF && R.n < R.N) ? 2 : 0;
-            const auto key = std::make_pair(std::make_pair(R.tile.block, R.tile.groups), flav);
+            // (a window-kernel tile runs the optimization on the table's)
+            const Tile t = have_tile(ctx->qtype, ctx->htype, R.tile.block, R.tile.groups) ? R.tile : default_tile(R.N);
+            const Exec x = exec_of(t, flav, R.asked, R.N, ctx->htype, false, ctx->num_chains);
+            const auto key = std::make_pair(std::make_pair(x.tile.block, x.tile.groups), x.flav);
             if (!class_of.count(key)) {
                 class_of[key] = ctx->opt_classes.size();
                 LaunchClass k;
-                // (a window-kernel tile runs the optimization on the table's)
-                k.tile = have_tile(ctx->qtype, ctx->htype, R.tile.block, R.tile.groups) ? R.tile : default_tile(R.N);
-                k.flav = flav;
+                k.tile = x.tile;
+                k.flav = x.flav;
                 k.dyn = 0;
                 ctx->opt_classes.push_back(k);
             }
             LaunchClass& K = ctx->opt_classes[class_of[key]];
-            K.dyn = std::max(K.dyn, (size_t)R.pitch * 4 * (flav == 2 ? 2 : 1));
+            K.dyn = std::max(K.dyn, dyn_lds(x.flav, R.pitch));
             for (int32_t c = 0; c < R.chains; ++c) K.chains.push_back(R.chain_begin + c);
         }
         for (auto& k : ctx->opt_classes) {

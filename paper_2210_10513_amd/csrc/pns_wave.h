@@ -60,13 +60,6 @@ __device__ __forceinline__ uint32_t get_bit(const uint32_t (&xw)[NW], int i)
     return (xw[i >> 5] >> (i & 31)) & 1u;
 }
 
-// body(integral_constant<i>) for every i of the sequence, in order.
-template <int... I, typename Fn>
-__device__ __forceinline__ void for_each_index(std::integer_sequence<int, I...>, Fn&& body)
-{
-    (body(std::integral_constant<int, I>{}), ...);
-}
-
 // The lane's index in its wave, formed where it is used: a per-lane value
 // kept across the step loop takes a register or is spilled and reloaded.
 __device__ __forceinline__ int lane_here()
@@ -361,10 +354,10 @@ void wave_kernel(const StepArgs a)
                 }
             };
             // the groups the window meets, tested four at a time
-            for_each_index(std::make_integer_sequence<int, (G + 3) / 4>{}, [&](auto qc) {
+            step::for_each_index(std::make_integer_sequence<int, (G + 3) / 4>{}, [&](auto qc) {
                 constexpr int q = decltype(qc)::value;
                 if ((gmask >> (4 * q)) & 0xFull) {
-                    for_each_index(std::make_integer_sequence<int, 4>{}, [&](auto vc) {
+                    step::for_each_index(std::make_integer_sequence<int, 4>{}, [&](auto vc) {
                         constexpr int g = 4 * q + decltype(vc)::value;
                         if constexpr (g < G) {
                             if ((gmask >> g) & 1ull) weigh(std::integral_constant<int, g>{});

@@ -1,0 +1,139 @@
+"""GPU tests of the kernel that runs all-bits and drawn-subset problems whose
+tile the caller left open: its records, states, outputs and counters equal the
+step kernel's (an explicit tile) bit for bit at the edges of its tiles, for
+every field type, mode, launch form and kind of run."""
+import numpy as np
+import pytest
+
+from paper_2210_10513_amd import inputs
+from paper_2210_10513_amd.binding import Sampler
+
+pytestmark = pytest.mark.gpu
+
+TILES = {256: (64, 1), 512: (128, 1), 1024: (256, 1), 2048: (256, 2), 4096: (256, 4), 8192: (512, 4), 16384: (1024, 4)}
+
+
+def _problem(kind, N, seed=0):
+    """(Q, beta, layout); i64: int32 entries whose field bound needs 64 bits."""
+    rng = np.random.default_rng(N + seed)
+    if kind == "f32":
+        A = (rng.standard_normal((N, N)) / np.sqrt(N)).astype(np.float32)
+        return np.triu(A) + np.triu(A, 1).T, 1.0, "symmetric"
+    if kind == "i64":
+        hi = 2**29
+        Q = np.triu(rng.integers(-hi, hi + 1, (N, N), dtype=np.int32))
+        return Q, 4.0 / (hi * np.sqrt(N)), "upper"
+    Q = inputs.symmetric_int(N, -100, 100, np.int16 if kind == "i16" else np.int32, seed=N + seed, density=0.5)
+    return Q, 0.01 * np.sqrt(2048.0 / N), "symmetric"
+
+
+def _step_tile(N):
+    return TILES[min(t for t in TILES if t >= N)]
+
+
+def _same(a, b):
+    assert set(a) == set(b)
+    for k in a:
+        assert np.array_equal(a[k], b[k], equal_nan=a[k].dtype.kind == "f"), k
+
+
+def _state(s, log=False):
+    out = {f"cur_{k}": v for k, v in s.read_current().items()}
+    out.update({f"stat_{k}": v for k, v in s.stats().items()})
+    for k, v in zip(("s", "m", "e"), s.read()):
+        out[f"rec_{k}"] = v
+    if log:
+        out.update({f"log_{k}": v for k, v in s.read_log().items()})
+    return out
+
+
+def _pair(Q, beta, n, mode, layout, chains, fn, **kw):
+    out = []
+    for tile in ((0, 0), _step_tile(Q.shape[0])):
+        s = Sampler(Q, beta, n, mode, num_chains=chains, layout=layout, seed=11, block=tile[0], groups=tile[1], **kw)
+        out.append(fn(s))
+        s.close()
+    _same(out[0], out[1])
+    return out[0]
+
+
+# (N, chains): both sides of each line of the tile rule and ragged sizes between
+SIZES = [(1, 3), (5, 3), (256, 3), (257, 3), (511, 600), (513, 3), (513, 600), (768, 600), (769, 600), (1000, 3),
+         (1025, 3), (1030, 600), (2049, 3), (3000, 2), (3073, 2), (3073, 600), (4097, 2), (6145, 2)]
+
+
+@pytest.mark.parametrize("kind", ["i16", "i32", "i64", "f32"])
+@pytest.mark.parametrize("N,chains", SIZES)
+def test_records_equal_the_step_kernels(kind, N, chains):
+    Q, beta, layout = _problem(kind, N)
+    for mode, n in (("rf", 0), ("basic", max(1, N // 3)), ("basic", 1), ("unbiased_rand", max(1, N // 9))):
+        _pair(Q, beta, n, mode, layout, chains, lambda s: _state(s.run(45), log=True), log_capacity=45, L0=30)
+
+
+@pytest.mark.parametrize("kind", ["i16", "f32", "i64"])
+@pytest.mark.parametrize("N", [8193, 12001])
+def test_records_of_the_widest_tile(kind, N):
+    Q, beta, layout = _problem(kind, N)
+    for mode, n in (("rf", 0), ("basic", 999)):
+        _pair(Q, beta, n, mode, layout, 2, lambda s: _state(s.run(25), log=True), log_capacity=25)
+
+
+@pytest.mark.parametrize("kind", ["i16", "i64", "f32"])
+@pytest.mark.parametrize("N,n", [(200, 24), (700, 64), (1500, 100)])
+def test_kinds_of_run_equal(kind, N, n):
+    """Exact-time, optimization and resumed runs, snapshots, launch forms."""
+    Q, beta, layout = _problem(kind, N)
+
+    def runs(s):
+        out = {}
+        if s.mode in (0, 1):  # (runs of original samples: Rejection-Free and Basic PNS)
+            s.run_original(900)
+        else:
+            s.run(30)
+        out.update({f"a_{k}": v for k, v in _state(s).items()})
+        s.optimize(40, 0.7)
+        out["best_s"], out["best_e"] = s.read_best()
+        s.adopt_best().run(33)
+        out.update({f"b_{k}": v for k, v in _state(s).items()})
+        buf = s.save()
+        s.run(21)
+        out.update({f"c_{k}": v for k, v in _state(s).items()})
+        s.load(buf).run(21)
+        for k, v in _state(s).items():
+            if not k.startswith("stat_"):
+                assert np.array_equal(out[f"c_{k}"], v, equal_nan=v.dtype.kind == "f"), k
+        return out
+
+    for mode, m in (("rf", 0), ("basic", n), ("unbiased_rand", n)):
+        plain = _pair(Q, beta, m, mode, layout, 3, runs, launch="plain", chunk=7)
+        graph = _pair(Q, beta, m, mode, layout, 3, runs, launch="graph", chunk=7)
+        _same(plain, graph)
+
+        def snaps(s):
+            s.run(60)
+            x, w, e, cnt = s.read_snapshots()
+            return {"x": x, "w": w, "e": e, "cnt": np.asarray(cnt), "rb": s.rb_weights()["snap"]}
+
+        _pair(Q, beta, m, mode, layout, 3, snaps, snapshot_every=4, snapshot_capacity=15)
+
+
+@pytest.mark.parametrize("kind,scale", [("i16", 40.0), ("i32", 4000.0), ("f32", 3000.0), ("i64", 1e4)])
+def test_rescaled_and_overflowing_weights_equal(kind, scale):
+    """Large beta: weights past the tables, sums that vanish and are rescaled,
+    saturated multiplicities."""
+    for N, n in ((13, 2), (300, 5), (900, 40)):
+        Q, beta, layout = _problem(kind, N, seed=3)
+        for mode, m in (("rf", 0), ("basic", n), ("unbiased_rand", n)):
+            _pair(Q, beta * scale, m, mode, layout, 4, lambda s: _state(s.run(80), log=True), log_capacity=80, L0=20)
+
+
+def test_histogram_equal():
+    for kind in ("i16", "f32"):
+        Q, beta, layout = _problem(kind, 12)
+        for mode, m in (("rf", 0), ("basic", 5), ("unbiased_rand", 5)):
+            def hist(s):
+                s.run(500)
+                w, v = s.read_hist()
+                return {"w": w, "v": v, "rb": s.rb_weights()["hist"]}
+            got = _pair(Q, beta, m, mode, layout, 1, hist, hist=True)
+            assert got["v"].sum() > 0
