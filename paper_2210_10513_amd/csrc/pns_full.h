@@ -69,6 +69,17 @@ __device__ __forceinline__ int count_below(uint64_t m)
     return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
+// Chains of one wave that share a workgroup.  The waves of a workgroup go to
+// different SIMDs of a compute unit; workgroups of one wave may meet on one: the
+// first launch of 1024 chains after a kernel of larger workgroups took 3.74 ms
+// where the later ones took 2.84 (2000 steps, N = 1024 int16).  Up to one chain
+// per compute unit there is nothing to share.
+constexpr int kMaxShare = 4;
+constexpr int share_of(int32_t chains) { return chains <= 256 ? 1 : chains <= 512 ? 2 : kMaxShare; }
+
+constexpr int kTableBytes = 8 * (2 * kTabLo + kTabHi);
+typedef const __attribute__((address_space(3))) double* LdsDouble;
+
 // Waves per SIMD asked of the compiler: as many as leave the plain kernels
 // without (or nearly without) spilled registers, one fewer for the kernels with
 // a budget.
@@ -95,8 +106,9 @@ __device__ __forceinline__ Args args_here()
 // PLAIN: Rejection-Free or Basic PNS sampling without a time limit, where no
 // budget steers the chain; else Unbiased PNS, exact-time and optimization runs.
 template <typename QT, typename HT, int W, int G, bool DRAWN, bool INSTR, bool PLAIN>
-__global__ __attribute__((amdgpu_flat_work_group_size(64 * W, 64 * W), amdgpu_waves_per_eu(waves_per_eu<HT, G, PLAIN>())))
-void full_kernel(const StepArgs a)
+__global__ __attribute__((amdgpu_flat_work_group_size(64 * W, W == 1 ? 64 * kMaxShare : 64 * W),
+                          amdgpu_waves_per_eu(waves_per_eu<HT, G, PLAIN>())))
+void full_kernel(const StepArgs a, const int32_t chains, const int32_t share, const int32_t stride)
 {
     // A weight is the rounded product of its two table entries, summed as such.
 #pragma clang fp contract(off)
@@ -113,9 +125,15 @@ void full_kernel(const StepArgs a)
     static_assert(NSEG <= 64 && F <= 32, "one segment scan, one word of bits per lane");
     using QW = typename step::Wide<QT>::T;
 
-    __shared__ double tab_lo[kInt ? 2 * kTabLo : 1];  // [kTabLo, 2 kTabLo): zeros, for bits outside the subset
-    __shared__ double tab_hi[kInt ? kTabHi : 1];
+    // One wave: `share` chains to a workgroup, each with its tables in its part
+    // (`stride` bytes) of the dynamic LDS; else static tables and one chain.
+    __shared__ double tabs[kInt && W > 1 ? 2 * kTabLo + kTabHi : 1];
     __shared__ double etab[kInt ? 1 : 64][2];
+    extern __shared__ double lds[];
+    const int part_of = W > 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    char* const mine = reinterpret_cast<char*>(lds) + (W > 1 ? 0 : part_of * stride);
+    double* const tab_hi = W > 1 ? tabs : reinterpret_cast<double*>(mine);
+    double* const tab_lo = tab_hi + kTabHi;  // [kTabLo, 2 kTabLo): zeros, for bits outside the subset
     // exchanges between waves (W > 1), the totals in two buffers (even, odd steps)
     __shared__ double seg_sum[2][W > 1 ? NSEG : 1];
     __shared__ double mx_part[W];
@@ -123,13 +141,16 @@ void full_kernel(const StepArgs a)
     // drawn subsets: the waves' counts of first occurrences (two buffers) and
     // the members' bits per lane; own [pitch] (dynamic) the first occurrences
     __shared__ int32_t cnt[2][W];
-    __shared__ uint32_t memw[DRAWN ? BLOCK : 1];
-    extern __shared__ uint32_t own[];
+    __shared__ uint32_t members[DRAWN && W > 1 ? BLOCK : 1];
+    uint32_t* const memw = W > 1 ? members : reinterpret_cast<uint32_t*>(mine + (kInt ? kTableBytes : 0));
+    uint32_t* const own = W > 1 ? reinterpret_cast<uint32_t*>(lds) : memw + BLOCK;
 
-    const int tid = threadIdx.x;
+    const int tid = W > 1 ? (int)threadIdx.x : (int)threadIdx.x & 63;
     const int lane = tid & 63;
     const int wave = W > 1 ? __builtin_amdgcn_readfirstlane(tid >> 6) : 0;
-    const int chain = a.chain_list ? a.chain_list[blockIdx.x] : a.chain_first + (int)blockIdx.x;
+    const int index = W > 1 ? (int)blockIdx.x : (int)blockIdx.x * share + part_of;
+    if (W == 1 && index >= chains) return;  // (no barrier follows)
+    const int chain = a.chain_list ? a.chain_list[index] : a.chain_first + index;
     const Problem P = a.problems[a.chain_problem[chain]];
     const int32_t N = P.N;
     const int64_t pitch = P.pitch;
@@ -209,12 +230,14 @@ void full_kernel(const StepArgs a)
     uint32_t mem = valid;
     const bool part = N != 4 * BLOCK * G;  // some of the tile's bits do not exist
     const bool masked = DRAWN || part;
-    // one-group integer offsets of the zero slots (bytes), kept with the subset
+    // integer problems: where the zero slots are (bytes), kept with the subset
+    const uint32_t tab_at = (uint32_t)(uintptr_t)(LdsDouble)tab_hi;
+    const uint32_t zo_at = W > 1 ? 0u : tab_at + (uint32_t)(8 * kTabHi);
     uint32_t zo[kInt ? F : 1];
     auto set_zo = [&]() {
         if constexpr (kInt) {
 #pragma unroll
-            for (int i = 0; i < F; ++i) zo[i] = (~(mem >> i) & 1u) * (uint32_t)(8 * kTabLo);
+            for (int i = 0; i < F; ++i) zo[i] = (~(mem >> i) & 1u) * (uint32_t)(8 * kTabLo) + zo_at;
         }
     };
     uint32_t tag = kDraws;  // number of the next draw (falling)
@@ -272,7 +295,7 @@ void full_kernel(const StepArgs a)
             memw[tid] = 0u;  // (the next draw's members follow its exchange of occurrences)
         }
     };
-    __syncthreads();  // tables ready
+    exchange<W>();  // tables ready
     if constexpr (DRAWN) {
         if (!unbiased || k == 0) {
             draw(k);
@@ -352,11 +375,20 @@ void full_kernel(const StepArgs a)
                 emax = emax > e[i] ? emax : e[i];
                 const HT e0 = e[i] > 0 ? e[i] : 0;
                 const uint32_t ep = (uint32_t)(e0 < (HT)(kTabMax - 1) ? e0 : (HT)(kTabMax - 1));
-                // tab_hi[ep >> 6] and tab_lo[ep & 63], or a zero slot, by byte offset
-                const char* ph = reinterpret_cast<const char*>(tab_hi) + ((ep >> 3) & (uint32_t)(8 * (kTabHi - 1)));
-                const char* pl = reinterpret_cast<const char*>(tab_lo) + (((ep << 3) & (uint32_t)(8 * (kTabLo - 1))) | zo[i]);
-                th[i] = *reinterpret_cast<const double*>(ph);
-                tl[i] = *reinterpret_cast<const double*>(pl);
+                // tab_hi[ep >> 6] and tab_lo[ep & 63], or a zero slot, two instructions
+                // each: a byte offset from a constant place, or (one wave) a field of
+                // ep, which the asm keeps apart, shifted and added to the table's
+                if constexpr (W > 1) {
+                    const char* ph = reinterpret_cast<const char*>(tab_hi) + ((ep >> 3) & (uint32_t)(8 * (kTabHi - 1)));
+                    const char* pl = reinterpret_cast<const char*>(tab_lo) + (((ep << 3) & (uint32_t)(8 * (kTabLo - 1))) | zo[i]);
+                    th[i] = *reinterpret_cast<const double*>(ph);
+                    tl[i] = *reinterpret_cast<const double*>(pl);
+                } else {
+                    uint32_t hi = ep >> 6, lo = ep & (uint32_t)(kTabLo - 1);
+                    asm("" : "+v"(hi), "+v"(lo));
+                    th[i] = *reinterpret_cast<LdsDouble>((uintptr_t)((hi << 3) + tab_at));
+                    tl[i] = *reinterpret_cast<LdsDouble>((uintptr_t)((lo << 3) + zo[i]));
+                }
             }
 #pragma unroll
             for (int i = 0; i < F; ++i) w[i] = th[i] * tl[i];
@@ -835,10 +867,15 @@ void full_kernel(const StepArgs a)
 template <typename QT, typename HT, int W, int G, bool DRAWN, bool INSTR>
 hipError_t launch_one(int32_t grid, size_t dyn, hipStream_t st, const StepArgs& a)
 {
+    // dyn: the table of first occurrences
+    const int32_t share = W == 1 ? share_of(grid) : 1;
+    const bool tables = W == 1 && !std::is_floating_point<HT>::value;
+    const size_t stride = (tables ? kTableBytes : 0) + (DRAWN ? (W == 1 ? 4 * 64 : 0) + dyn : 0);
+    const dim3 blocks((grid + share - 1) / share), threads(64 * W * share);
     if (a.mode <= step::kModeBasic && a.orig_time == 0)
-        hipLaunchKernelGGL((full_kernel<QT, HT, W, G, DRAWN, INSTR, true>), dim3(grid), dim3(64 * W), dyn, st, a);
+        hipLaunchKernelGGL((full_kernel<QT, HT, W, G, DRAWN, INSTR, true>), blocks, threads, share * stride, st, a, grid, share, (int32_t)stride);
     else
-        hipLaunchKernelGGL((full_kernel<QT, HT, W, G, DRAWN, INSTR, false>), dim3(grid), dim3(64 * W), dyn, st, a);
+        hipLaunchKernelGGL((full_kernel<QT, HT, W, G, DRAWN, INSTR, false>), blocks, threads, share * stride, st, a, grid, share, (int32_t)stride);
     return hipGetLastError();
 }
 
