@@ -300,6 +300,11 @@ Tile default_tile_for(int32_t mode, int32_t N, int32_t n, int32_t qtype, int32_t
 //   * floats weigh with the exponential itself: one group per lane up to two
 //     chains per CU, and at all counts for N > 768 without a drawn subset
 //     (1024 chains of N = 1000: 2.3, one wave 2.6, the step kernel 2.4).
+// Systematic windows of integers run the window kernel, one or two waves per
+// chain, where the step kernel's workgroups no longer share the chip in one
+// round (chains, step / window kernel: N = 700 4096 8.7 / 5.4; N = 1500 768 2.26 /
+// 2.27, 1024 4.2 / 2.3; N = 3000 512 2.5 / 2.7, 768 4.7 / 2.9; N = 8000 768 4.0 /
+// 3.8, 1024 6.8 / 4.3), and at all counts up to 512 bits (64 chains 1.8 / 1.5).
 // The step kernel stays where it is the faster one: int64 fields up to 1024
 // bits (256 chains of N = 1000: 1.9 against 2.3) and random sets of int64
 // fields (2.2 against 2.8), random sets of floats above 512 up to 1024 bits
@@ -310,9 +315,24 @@ struct Exec {
     int32_t flav;
 };
 
-Exec exec_of(Tile tile, int32_t flav, bool asked, int32_t N, int32_t htype, bool random_sets, int64_t chains)
+Exec exec_of(Tile tile, int32_t flav, bool asked, int32_t N, int32_t n, int32_t qtype, int32_t htype, int32_t mode, bool hist,
+             int64_t chains)
 {
-    if (asked || (flav != 0 && flav != 2)) return {tile, flav};
+    const bool random_sets = mode == PNS_MODE_UNBIASED_RAND;
+    if (asked || flav == 5) return {tile, flav};
+    if (flav != 0 && flav != 2) {
+        if (mode != PNS_MODE_UNBIASED_SYS || hist) return {tile, flav};
+        const Tile t = N <= 512    ? Tile{64, 2}
+                       : N <= 1024 ? Tile{64, 4}
+                       : N <= 2048 ? Tile{64, 8}
+                       : N <= 4096 ? Tile{64, 16}
+                       : N <= 6144 ? Tile{64, 24}
+                                   : Tile{128, 16};
+        const int64_t most = N <= 512 ? 0 : N <= 1024 ? 1024 : N > 2048 && N <= 4096 ? 512 : 768;
+        if (N <= 8192 && chains > most && have_wave_tile(qtype, htype, t.block, t.groups) && window_slots_ok(N, n, t.block, t.groups))
+            return {t, 5};
+        return {tile, flav};
+    }
     const bool drawn = flav == 2, few = chains <= 512;
     const bool f64 = htype == H_F64, i64 = htype == H_I64;
     if (i64 && (drawn ? random_sets : N <= 1024)) return {tile, flav};
@@ -908,7 +928,7 @@ int create_impl(pns_ctx** out, std::vector<ProblemSpec>& specs, int32_t mode, co
         R.tile = S.tile;
         R.flav = flav[p];
         R.asked = S.asked;
-        R.exec = exec_of(S.tile, flav[p], S.asked, S.N, htype, mode == PNS_MODE_UNBIASED_RAND, total_chains);
+        R.exec = exec_of(S.tile, flav[p], S.asked, S.N, S.n, qtype, htype, mode, o.hist, total_chains);
         ctx->probs.push_back(R);
         ProblemRun& RR = ctx->probs.back();
         int r = dev_alloc(reinterpret_cast<uint8_t**>(&RR.A), pp[p]->A.size() + kRowTailBytes);
@@ -1179,7 +1199,7 @@ int reconfigure(pns_ctx* ctx, Tile t, int32_t n)
     D.s = R.s;
     D.qtype = ctx->qtype;
     HIP_TRY(hipMemcpy(ctx->problems, &D, sizeof(Problem), hipMemcpyHostToDevice), "reconfigure");
-    R.exec = exec_of(t, R.flav, false, R.N, ctx->htype, ctx->mode == PNS_MODE_UNBIASED_RAND, ctx->num_chains);
+    R.exec = exec_of(t, R.flav, false, R.N, R.n, ctx->qtype, ctx->htype, ctx->mode, false, ctx->num_chains);
     LaunchClass& K = ctx->classes[0];
     K.tile = R.exec.tile;
     K.flav = R.exec.flav;
@@ -2302,7 +2322,7 @@ int pns_optimize(pns_ctx* ctx, int64_t steps, double temperature)
             const int32_t flav = (ctx->mode != PNS_MODE_RF && R.n < R.N) ? 2 : 0;
             // (a window-kernel tile runs the optimization on the table's)
             const Tile t = have_tile(ctx->qtype, ctx->htype, R.tile.block, R.tile.groups) ? R.tile : default_tile(R.N);
-            const Exec x = exec_of(t, flav, R.asked, R.N, ctx->htype, false, ctx->num_chains);
+            const Exec x = exec_of(t, flav, R.asked, R.N, R.n, ctx->qtype, ctx->htype, PNS_MODE_BASIC, false, ctx->num_chains);
             const auto key = std::make_pair(std::make_pair(x.tile.block, x.tile.groups), x.flav);
             if (!class_of.count(key)) {
                 class_of[key] = ctx->opt_classes.size();

@@ -43,11 +43,19 @@ constexpr int kSlots = 4;
 // Energy difference slot value of a bit outside the window.
 constexpr int32_t kOut = INT32_MIN;
 
-// Waves per SIMD asked of the compiler: the fields take F = 4 G registers.
-template <int W, int G>
+// Waves per SIMD asked of the compiler: the fields take F = 4 G registers and
+// the row of a flip as many for 32-bit coefficients (row_groups at a time), half
+// for 16-bit ones.  With three waves the int32 tiles of 16 groups spilled 84
+// registers a lane: 4096 chains of N = 4000, n = 250 took 35 us per step.
+template <typename QT, int G>
 constexpr int waves_per_eu()
 {
-    return G <= 8 ? 4 : (G <= 16 ? 3 : 2);
+    return G <= 8 ? 4 : (G <= 16 && sizeof(QT) == 2 ? 3 : 2);
+}
+template <typename QT, int G>
+constexpr int row_groups()
+{
+    return sizeof(QT) == 4 && G > 16 ? G / 2 : G;
 }
 
 // Two 16-bit integers of one register (operands of the 16-bit dot product).
@@ -115,9 +123,35 @@ __device__ __noinline__ double exp_weight(double beta, int32_t e, double shift)
 
 __device__ __noinline__ double exp_of(double x) { return exp(x); }
 
+// Chains of one wave that share a workgroup: the waves of a workgroup go to
+// different SIMDs of a compute unit, those of several one-wave workgroups may
+// meet on one (2000 steps of 1024 chains, N = 2000, n = 128: 4.6 ms in the first
+// launch after a kernel of larger workgroups, 2.7 in the later ones).
+constexpr int kMaxShare = 4;
+constexpr int share_of(int32_t chains) { return chains <= 256 ? 1 : chains <= 512 ? 2 : kMaxShare; }
+
+// LDS of a chain.
+template <int W, int G>
+struct Lds {
+    // energy differences of the window's groups, per wave and slot (kOut
+    // outside the window), and the inclusive scans of their four-bit sums
+    int4 eslot[W][kSlots][64];
+    double islot[W][kSlots][64];
+    // tab_lo[64 .. 128) = 0: the weight of a bit outside the window
+    double tab_lo[2 * kTabLo];
+    double tab_hi[kTabHi];
+    // per-step exchanges, two buffers (even and odd steps): a wave may write
+    // the next step's while another wave still reads this step's
+    double seg_sum[2][G * W];
+    double mx_part[W];
+    int64_t xchg[2];
+    int32_t slow_part[2][W];
+};
+
 template <typename QT, int W, int G, bool INSTR>
-__global__ __attribute__((amdgpu_flat_work_group_size(64 * W, 64 * W), amdgpu_waves_per_eu(waves_per_eu<W, G>())))
-void wave_kernel(const StepArgs a)
+__global__ __attribute__((amdgpu_flat_work_group_size(64 * W, W == 1 ? 64 * kMaxShare : 64 * W),
+                          amdgpu_waves_per_eu(waves_per_eu<QT, G>())))
+void wave_kernel(const StepArgs a, const int32_t chains, const int32_t share)
 {
     // A weight is the rounded product of its two table entries, summed as
     // such (no fused multiply-add into the sums), as in the step kernel.
@@ -131,24 +165,25 @@ void wave_kernel(const StepArgs a)
     using step::small_scan;
     using step::wave_scan;
 
-    // tab_lo[64 .. 128) = 0: the weight of a bit outside the window
-    __shared__ double tab_lo[2 * kTabLo];
-    __shared__ double tab_hi[kTabHi];
-    // per-step exchanges, two buffers (even and odd steps): a wave may write
-    // the next step's while another wave still reads this step's
-    __shared__ double seg_sum[2][NSEG];
-    __shared__ int32_t slow_part[2][W];
-    __shared__ double mx_part[W];
-    __shared__ int64_t xchg[2];
-    // energy differences of the window's groups, per wave and slot (kOut
-    // outside the window), and the inclusive scans of their four-bit sums
-    __shared__ int4 eslot[W][kSlots][64];
-    __shared__ double islot[W][kSlots][64];
+    // One wave: `share` chains to a workgroup, each with its part of the LDS.
+    extern __shared__ double2 lds[];
+    const int part = W > 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    Lds<W, G>& mine = reinterpret_cast<Lds<W, G>*>(lds)[part];
+    auto& tab_lo = mine.tab_lo;
+    auto& tab_hi = mine.tab_hi;
+    auto& seg_sum = mine.seg_sum;
+    auto& slow_part = mine.slow_part;
+    auto& mx_part = mine.mx_part;
+    auto& xchg = mine.xchg;
+    auto& eslot = mine.eslot;
+    auto& islot = mine.islot;
 
-    const int tid = threadIdx.x;
+    const int tid = W > 1 ? (int)threadIdx.x : (int)threadIdx.x & 63;
     const int lane = tid & 63;
     const int wave = W > 1 ? __builtin_amdgcn_readfirstlane(tid >> 6) : 0;
-    const int chain = a.chain_list ? a.chain_list[blockIdx.x] : a.chain_first + (int)blockIdx.x;
+    const int index = W > 1 ? (int)blockIdx.x : (int)blockIdx.x * share + part;
+    if (W == 1 && index >= chains) return;  // (no barrier follows)
+    const int chain = a.chain_list ? a.chain_list[index] : a.chain_first + index;
     const Problem P = a.problems[a.chain_problem[chain]];
     const int32_t N = P.N;
     const int64_t pitch = P.pitch;
@@ -251,7 +286,8 @@ void wave_kernel(const StepArgs a)
     };
     set_window(s0);
 
-    __syncthreads();  // tables ready
+    if constexpr (W > 1) __syncthreads();  // tables ready
+    else __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // (its own lanes' stores, in order)
 
     int64_t ub_base = k;
     Uniforms64 ub = uniforms64(cid, ub_base, seed, lane);
@@ -456,11 +492,12 @@ void wave_kernel(const StepArgs a)
 
         int32_t action = -1;
         int64_t M;
-        // the row of a move and, for 16-bit coefficients, the multiplier of
-        // its update, which runs after the two paths join (defined on both,
-        // so that the fields are not copied to other registers and back)
-        decltype(step::load_raw4(static_cast<const QT*>(nullptr))) raw[G];
-        [[maybe_unused]] int32_t mult = 0;
+        // the row of a move (its first kRow groups) and the multiplier of its
+        // update, which runs after the two paths join (defined on both, so
+        // that the fields are not copied to other registers and back)
+        constexpr int kRow = row_groups<QT, G>();
+        decltype(step::load_raw4(static_cast<const QT*>(nullptr))) raw[kRow];
+        int32_t mult = 0;
         if (stay) {
             // stay L times and move to the next systematic set
             M = L;
@@ -473,10 +510,11 @@ void wave_kernel(const StepArgs a)
             // (the fields stay where the move path updates them in place)
 #pragma unroll
             for (int i = 0; i < F; ++i) asm volatile("" : "+v"(u[i]));
-            if constexpr (sizeof(QT) == 2) {
-                // (no row: the registers as they are, unused on this path)
+            // (no row: the registers as they are, unused on this path)
 #pragma unroll
-                for (int g = 0; g < G; ++g) asm volatile("" : "=v"(raw[g].x), "=v"(raw[g].y));
+            for (int g = 0; g < kRow; ++g) {
+                if constexpr (sizeof(QT) == 2) asm volatile("" : "=v"(raw[g].x), "=v"(raw[g].y));
+                else asm volatile("" : "=v"(raw[g].x), "=v"(raw[g].y), "=v"(raw[g].z), "=v"(raw[g].w));
             }
         } else {
             // ---- proportional choice (appendix "How to Sample
@@ -576,7 +614,7 @@ void wave_kernel(const StepArgs a)
             // matrix's tail padding and drop what they read)
             const QT* row = reinterpret_cast<const QT*>(P.A) + (int64_t)c * pitch + (wave * 64 + lane_here()) * 4;
 #pragma unroll
-            for (int g = 0; g < G; ++g) raw[g] = step::load_raw4(row + g * BLOCK * 4);
+            for (int g = 0; g < kRow; ++g) raw[g] = step::load_raw4(row + g * BLOCK * 4);
             const int cl = (c >> 2) % BLOCK;
             const int ci = ((c >> 2) / BLOCK) * 4 + (c & 3);
             if (wave * 64 + lane_here() == cl) {
@@ -593,26 +631,7 @@ void wave_kernel(const StepArgs a)
             M = m;
             action = c;
             ++c_flips;
-            if constexpr (sizeof(QT) == 2) {
-                mult = __builtin_amdgcn_readfirstlane(xc ? -s : s);
-            } else {
-                const int sh = s - 1;
-                if (xc) {
-#pragma unroll
-                    for (int g = 0; g < G; ++g) {
-                        const auto r = step::widen4(raw[g]);
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) u[g * 4 + v] -= r.v[v] << sh;
-                    }
-                } else {
-#pragma unroll
-                    for (int g = 0; g < G; ++g) {
-                        const auto r = step::widen4(raw[g]);
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) u[g * 4 + v] += r.v[v] << sh;
-                    }
-                }
-            }
+            mult = __builtin_amdgcn_readfirstlane(xc ? -s : s);
         }
         if constexpr (sizeof(QT) == 2) {
             if (!stay) {
@@ -628,6 +647,32 @@ void wave_kernel(const StepArgs a)
                     u[g * 4 + 1] = __builtin_amdgcn_sdot2(p0, mhi, u[g * 4 + 1], false);
                     u[g * 4 + 2] = __builtin_amdgcn_sdot2(p1, mlo, u[g * 4 + 2], false);
                     u[g * 4 + 3] = __builtin_amdgcn_sdot2(p1, mhi, u[g * 4 + 3], false);
+                }
+            }
+        } else if (!stay) {
+            const int sh = s - 1;
+#pragma unroll
+            for (int g0 = 0; g0 < G; g0 += kRow) {
+                if (g0 > 0) {
+                    const QT* row = reinterpret_cast<const QT*>(P.A) + (int64_t)action * pitch + (wave * 64 + lane_here()) * 4;
+#pragma unroll
+                    for (int g = 0; g < kRow; ++g)
+                        raw[g] = step::load_raw4(row + (g0 + g) * BLOCK * 4);
+                }
+                if (mult < 0) {
+#pragma unroll
+                    for (int g = 0; g < kRow; ++g) {
+                        const auto r = step::widen4(raw[g]);
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) u[(g0 + g) * 4 + v] -= r.v[v] << sh;
+                    }
+                } else {
+#pragma unroll
+                    for (int g = 0; g < kRow; ++g) {
+                        const auto r = step::widen4(raw[g]);
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) u[(g0 + g) * 4 + v] += r.v[v] << sh;
+                    }
                 }
             }
         }
@@ -710,7 +755,10 @@ void wave_kernel(const StepArgs a)
 template <typename QT, int W, int G, bool INSTR>
 hipError_t launch_one(int32_t grid, hipStream_t st, const StepArgs& a)
 {
-    hipLaunchKernelGGL((wave_kernel<QT, W, G, INSTR>), dim3(grid), dim3(64 * W), 0, st, a);
+    static_assert(W > 1 || kMaxShare * sizeof(Lds<W, G>) <= 65536, "LDS of a workgroup");
+    const int32_t share = W == 1 ? share_of(grid) : 1;
+    hipLaunchKernelGGL((wave_kernel<QT, W, G, INSTR>), dim3((grid + share - 1) / share), dim3(64 * W * share),
+                       share * sizeof(Lds<W, G>), st, a, grid, share);
     return hipGetLastError();
 }
 

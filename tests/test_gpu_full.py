@@ -1,7 +1,8 @@
-"""GPU tests of the kernel that runs all-bits and drawn-subset problems whose
-tile the caller left open: its records, states, outputs and counters equal the
-step kernel's (an explicit tile) bit for bit at the edges of its tiles, for
-every field type, mode, launch form and kind of run."""
+"""GPU tests of the kernels that run problems whose tile the caller left open
+(all bits, drawn subsets, and systematic windows of integers): records, states,
+outputs and counters equal the step kernel's (an explicit tile) bit for bit at
+the edges of the tile rule, for every field type, mode, launch form and kind of
+run."""
 import numpy as np
 import pytest
 
@@ -137,3 +138,29 @@ def test_histogram_equal():
                 return {"w": w, "v": v, "rb": s.rb_weights()["hist"]}
             got = _pair(Q, beta, m, mode, layout, 1, hist, hist=True)
             assert got["v"].sum() > 0
+
+
+# (both sides of the chain counts where the window kernel takes over, its one-
+# and two-wave tiles, workgroups that are shared by two and four chains)
+@pytest.mark.parametrize("kind", ["i16", "i32"])
+@pytest.mark.parametrize("N,n,chains", [(200, 30, 3), (512, 100, 300), (700, 100, 1024), (700, 100, 1026),
+                                        (1500, 128, 770), (2050, 200, 515), (4000, 256, 513), (5000, 300, 769),
+                                        (7000, 256, 769), (9000, 256, 2)])
+def test_windows_equal_the_step_kernels(kind, N, n, chains):
+    Q, beta, layout = _problem(kind, N)
+    got = _pair(Q, beta, n, "unbiased_sys", layout, chains, lambda s: _state(s.run(40)), L0=30)
+    assert (got["stat_anomalies"] == 0).all()
+
+
+@pytest.mark.parametrize("N,tile", [(3000, (64, 16)), (5000, (64, 24)), (7000, (128, 16)), (9000, (128, 24)),
+                                    (16000, (256, 16))])
+def test_int32_rows_of_the_wide_window_tiles(N, tile):
+    """The row of a flip in one piece (16 groups) or two (24), both signs."""
+    Q, beta, layout = _problem("i32", N)
+    out = []
+    for block, groups in (tile, _step_tile(N)):
+        s = Sampler(Q, beta, 250, "unbiased_sys", num_chains=2, layout=layout, seed=4, init="random", block=block,
+                    groups=groups, log_capacity=120)
+        out.append(_state(s.run(120), log=True))
+        s.close()
+    _same(out[0], out[1])
