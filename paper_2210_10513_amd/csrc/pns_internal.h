@@ -175,6 +175,21 @@ hipError_t launch_moments_to_grad(double* G, int64_t n, double beta, const doubl
 // exits (a bounded delay between two groups of launches).
 hipError_t launch_hold(uint64_t ticks, hipStream_t st);
 
+// Chains' rows as a caller reads them: row row0 + i (chain (row0 + i) / per) of
+// `src`, at chain offset foff or (pitch > 0) at multiples of the pitch, to `dst`,
+// without gaps from row row0 (the first of its chain) on.  Sizes in elements.
+struct RowGather {
+    const void* src;
+    void* dst;
+    const int64_t* foff;
+    const int64_t* offsets;         // [chains + 1] sums of N
+    const int32_t* last_action;     // bit to flip back, or -1; or NULL
+    const int32_t* chain_problem;
+    const Problem* problems;
+    int64_t pitch, per, row0;
+};
+hipError_t launch_gather_rows(int32_t elem, int64_t rows, hipStream_t stream, const RowGather& args);
+
 // Fill `count` 64-bit words with a value (graph-safe alternative to memset).
 hipError_t launch_fill64(void* p, int64_t count, int64_t value, hipStream_t stream);
 

@@ -116,6 +116,20 @@ int dev_alloc(T** p, size_t count)
     return PNS_OK;
 }
 
+// Copy `bytes` of device memory to a caller buffer that is host or device;
+// complete on return.
+int dev_out(void* dst, const void* src, size_t bytes)
+{
+    if (dst == nullptr || bytes == 0) return PNS_OK;
+    if (is_device_ptr(dst)) {
+        HIP_TRY(hipMemcpy(dst, src, bytes, hipMemcpyDeviceToDevice), "copy to device buffer");
+        HIP_TRY(hipStreamSynchronize(nullptr), "copy to device buffer");
+    } else {
+        HIP_TRY(hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost), "download");
+    }
+    return PNS_OK;
+}
+
 template <typename T>
 int d2h(std::vector<T>& v, const void* src, size_t count)
 {
@@ -544,6 +558,11 @@ struct pns_ctx {
     Problem* problems = nullptr;
     int32_t* chain_problem = nullptr;
     int64_t* foff = nullptr;
+    int64_t* offsets = nullptr;  // h_offsets
+    int device = 0;              // the device of this memory
+    std::mutex rows_mutex;       // of rows_ws: gathered rows on their way to host memory
+    uint8_t* rows_ws = nullptr;
+    size_t rows_ws_bytes = 0;
     double* beta = nullptr;
     uint32_t* chain_id = nullptr;
     uint8_t* x = nullptr;
@@ -744,7 +763,7 @@ struct pns_ctx {
         if (graph) (void)hipGraphDestroy(graph);
         for (hipEvent_t ev : prof_ev)
             if (ev) (void)hipEventDestroy(ev);
-        void* ptrs[] = {problems, chain_problem, foff, beta, chain_id, x, h, fields_ws, rmem, E, L, sub, step, last_action, last_M,
+        void* ptrs[] = {problems, chain_problem, foff, offsets, rows_ws, beta, chain_id, x, h, fields_ws, rmem, E, L, sub, step, last_action, last_M,
                         last_E, counters, log_action, log_M, log_E, log_p, log_w, hist_w, hist_v, hist_rb,
                         snap_x, snap_M, snap_E, snap_w, snap_count};
         for (void* p : ptrs)
@@ -789,18 +808,89 @@ std::vector<double> energies_to_double(const pns_ctx* ctx, const std::vector<int
     return out;
 }
 
-// Per-chain padded rows -> concatenated rows of each chain's own N.
-template <typename T>
-std::vector<T> compact_rows(const pns_ctx* ctx, const std::vector<T>& padded, int64_t row_pitch, int64_t rows_per_chain)
+// `count` energies (int64 bits of the problem's kind) to a caller's buffer.
+int energies_out(const pns_ctx* ctx, double* dst, const int64_t* src, size_t count)
 {
-    std::vector<T> out((size_t)ctx->h_offsets.back() * rows_per_chain);
-    for (int32_t c = 0; c < ctx->num_chains; ++c) {
-        const int32_t N = ctx->probs[ctx->h_chain_problem[c]].N;
-        for (int64_t r = 0; r < rows_per_chain; ++r)
-            std::memcpy(&out[(size_t)(ctx->h_offsets[c] * rows_per_chain + r * N)],
-                        &padded[(size_t)((int64_t)c * rows_per_chain + r) * row_pitch], N * sizeof(T));
+    if (ctx->qtype == Q_F32) return dev_out(dst, src, count * 8);  // (their bits are doubles)
+    std::vector<int64_t> bits;
+    int rc = d2h(bits, src, count);
+    if (rc) return rc;
+    const std::vector<double> e = energies_to_double(ctx, bits);
+    return copy_out(dst, e.data(), count * 8);
+}
+
+// Largest piece of rows on its way to host memory (and largest rows_ws, unless
+// one chain's rows are more), and the size up to which the rows are copied whole
+// and sorted out on the host (two copies of some 15 us, no launch).
+constexpr size_t kRowsPiece = (size_t)32 << 20, kRowsSmall = (size_t)64 << 10;
+
+// Rows of `per` records of every chain (elements of `elem` bytes, padded as in
+// `src`: at h_foff, or every max_pitch elements) to a caller's buffer (host or
+// device) of concatenated rows of each chain's own N, without the padding;
+// last_action: device array of bits to flip back in the rows, or NULL.
+int rows_out(pns_ctx* ctx, void* dst, const void* src, size_t elem, bool by_pitch, int64_t per, const int32_t* last_action)
+{
+    const int64_t C = ctx->num_chains;
+    const size_t total = (size_t)ctx->h_offsets.back() * per * elem;
+    const size_t padded = (by_pitch ? (size_t)C * per * ctx->max_pitch : (size_t)ctx->fields) * elem;
+    hipPointerAttribute_t attr{};
+    const bool to_device = is_device_ptr(dst);
+    int now = 0;
+    HIP_TRY(hipGetDevice(&now), "current device");
+    // (another device's memory: through the host, as small rows)
+    const bool gather = now == ctx->device && C * per <= INT32_MAX && (!to_device || (hipPointerGetAttributes(&attr, dst) == hipSuccess &&
+                                                              attr.device == ctx->device));
+    RowGather a{src, dst, ctx->foff, ctx->offsets, last_action, ctx->chain_problem, ctx->problems,
+                by_pitch ? ctx->max_pitch : 0, per, 0};
+    if (gather && to_device) {
+        // (on the null stream, ordered as a copy to the buffer would be)
+        hipError_t e = launch_gather_rows((int32_t)elem, C * per, nullptr, a);
+        if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+        return e == hipSuccess ? PNS_OK : hip_fail(e, "rows to device buffer");
     }
-    return out;
+    if (gather && total > kRowsSmall) {
+        std::lock_guard<std::mutex> lock(ctx->rows_mutex);
+        size_t widest = 0;
+        for (const ProblemRun& R : ctx->probs) widest = std::max(widest, (size_t)R.N * per * elem);
+        const size_t want = std::min(total, std::max(kRowsPiece, widest));
+        if (ctx->rows_ws_bytes < want) {
+            if (ctx->rows_ws) (void)hipFree(ctx->rows_ws);
+            ctx->rows_ws_bytes = 0;
+            if (hipMalloc(reinterpret_cast<void**>(&ctx->rows_ws), want) == hipSuccess) ctx->rows_ws_bytes = want;
+            else (void)hipGetLastError(), ctx->rows_ws = nullptr;  // (no memory for it: the host sorts the rows out)
+        }
+        if (ctx->rows_ws) {
+            a.dst = ctx->rows_ws;
+            for (int64_t c = 0; c < C;) {
+                int64_t end = c + 1;
+                auto bytes = [&](int64_t to) { return (size_t)(ctx->h_offsets[to] - ctx->h_offsets[c]) * per * elem; };
+                while (end < C && bytes(end + 1) <= ctx->rows_ws_bytes) ++end;
+                a.row0 = c * per;
+                const hipError_t e = launch_gather_rows((int32_t)elem, (end - c) * per, nullptr, a);
+                if (e != hipSuccess) return hip_fail(e, "rows to host buffer");
+                HIP_TRY(hipMemcpy(static_cast<uint8_t*>(dst) + (size_t)ctx->h_offsets[c] * per * elem, ctx->rows_ws, bytes(end),
+                                  hipMemcpyDeviceToHost),
+                        "download");
+                c = end;
+            }
+            return PNS_OK;
+        }
+    }
+    std::vector<uint8_t> in, out(total);
+    std::vector<int32_t> la;
+    int rc = d2h(in, src, padded);
+    if (!rc && last_action) rc = d2h(la, last_action, C);
+    if (rc) return rc;
+    for (int64_t c = 0; c < C; ++c) {
+        const int32_t N = ctx->probs[ctx->h_chain_problem[c]].N;
+        for (int64_t r = 0; r < per; ++r) {
+            const size_t from = by_pitch ? (size_t)(c * per + r) * ctx->max_pitch : (size_t)ctx->h_foff[c];
+            uint8_t* to = &out[((size_t)ctx->h_offsets[c] * per + r * N) * elem];
+            std::memcpy(to, &in[from * elem], N * elem);
+            if (last_action && la[c] >= 0) to[la[c]] ^= 1u;
+        }
+    }
+    return copy_out(dst, out.data(), total);
 }
 
 // Everything a context needs, for one or several problems.
@@ -993,7 +1083,9 @@ int create_impl(pns_ctx** out, std::vector<ProblemSpec>& specs, int32_t mode, co
     } while (0)
     ALLOC(ctx->problems, Problem, specs.size());
     ALLOC(ctx->chain_problem, int32_t, C);
+    if (hipGetDevice(&ctx->device) != hipSuccess) return fail_free(fail(PNS_EDEVICE, "no current device"));
     ALLOC(ctx->foff, int64_t, C);
+    ALLOC(ctx->offsets, int64_t, C + 1);
     ALLOC(ctx->beta, double, C);
     ALLOC(ctx->chain_id, uint32_t, C);
     ALLOC(ctx->x, uint8_t, fields);
@@ -1045,6 +1137,7 @@ int create_impl(pns_ctx** out, std::vector<ProblemSpec>& specs, int32_t mode, co
     } while (0)
     H2D(ctx->problems, dev_probs.data(), dev_probs.size() * sizeof(Problem));
     H2D(ctx->chain_problem, ctx->h_chain_problem.data(), C * sizeof(int32_t));
+    H2D(ctx->offsets, ctx->h_offsets.data(), (C + 1) * sizeof(int64_t));
     H2D(ctx->foff, ctx->h_foff.data(), C * sizeof(int64_t));
     H2D(ctx->beta, betas.data(), C * sizeof(double));
     H2D(ctx->chain_id, cidv.data(), C * sizeof(uint32_t));
@@ -1705,28 +1798,14 @@ int pns_read(pns_ctx* ctx, uint8_t* states, int64_t* multiplicities, double* ene
     if (rc) return rc;
     const int64_t C = ctx->num_chains;
     if (states) {
-        std::vector<uint8_t> xp;
-        std::vector<int32_t> la;
-        if ((rc = d2h(xp, ctx->x, (size_t)ctx->fields))) return rc;
-        if ((rc = d2h(la, ctx->last_action, C))) return rc;
-        std::vector<uint8_t> xs((size_t)ctx->h_offsets.back());
-        for (int64_t c = 0; c < C; ++c) {
-            const int32_t N = ctx->probs[ctx->h_chain_problem[c]].N;
-            std::memcpy(&xs[ctx->h_offsets[c]], &xp[ctx->h_foff[c]], N);
-            if (la[c] >= 0) xs[ctx->h_offsets[c] + la[c]] ^= 1u;  // the record's state is before the last move
-        }
-        if ((rc = copy_out(states, xs.data(), xs.size()))) return rc;
+        // (the record's state is before the last move)
+        if ((rc = rows_out(ctx, states, ctx->x, 1, false, 1, ctx->last_action))) return rc;
     }
     if (multiplicities) {
-        std::vector<int64_t> m;
-        if ((rc = d2h(m, ctx->last_M, C))) return rc;
-        if ((rc = copy_out(multiplicities, m.data(), C * 8))) return rc;
+        if ((rc = dev_out(multiplicities, ctx->last_M, C * 8))) return rc;
     }
     if (energies) {
-        std::vector<int64_t> eb;
-        if ((rc = d2h(eb, ctx->last_E, C))) return rc;
-        std::vector<double> e = energies_to_double(ctx, eb);
-        if ((rc = copy_out(energies, e.data(), C * 8))) return rc;
+        if ((rc = energies_out(ctx, energies, ctx->last_E, C))) return rc;
     }
     return PNS_OK;
 }
@@ -1774,33 +1853,19 @@ int pns_read_current(pns_ctx* ctx, uint8_t* states, double* energies, void* fiel
     if (rc) return rc;
     const int64_t C = ctx->num_chains;
     if (states) {
-        std::vector<uint8_t> xp;
-        if ((rc = d2h(xp, ctx->x, (size_t)ctx->fields))) return rc;
-        std::vector<uint8_t> xs((size_t)ctx->h_offsets.back());
-        for (int64_t c = 0; c < C; ++c)
-            std::memcpy(&xs[ctx->h_offsets[c]], &xp[ctx->h_foff[c]], ctx->probs[ctx->h_chain_problem[c]].N);
-        if ((rc = copy_out(states, xs.data(), xs.size()))) return rc;
+        if ((rc = rows_out(ctx, states, ctx->x, 1, false, 1, nullptr))) return rc;
     }
     if (energies) {
-        std::vector<int64_t> eb;
-        if ((rc = d2h(eb, ctx->E, C))) return rc;
-        std::vector<double> e = energies_to_double(ctx, eb);
-        if ((rc = copy_out(energies, e.data(), C * 8))) return rc;
+        if ((rc = energies_out(ctx, energies, ctx->E, C))) return rc;
     }
     if (fields) {
         const size_t hb = ctx->htype == H_I32 ? 4 : 8;
-        std::vector<uint8_t> hp, hs((size_t)ctx->h_offsets.back() * hb);
-        if ((rc = d2h(hp, ctx->h, (size_t)ctx->fields * hb))) return rc;
-        for (int64_t c = 0; c < C; ++c)
-            std::memcpy(&hs[ctx->h_offsets[c] * hb], &hp[ctx->h_foff[c] * hb], ctx->probs[ctx->h_chain_problem[c]].N * hb);
-        if ((rc = copy_out(fields, hs.data(), hs.size()))) return rc;
+        if ((rc = rows_out(ctx, fields, ctx->h, hb, false, 1, nullptr))) return rc;
     }
     const std::pair<int64_t*, int64_t*> arrs[] = {{L, ctx->L}, {set_index, ctx->sub}, {step, ctx->step}};
     for (const auto& pr : arrs) {
         if (!pr.first) continue;
-        std::vector<int64_t> v;
-        if ((rc = d2h(v, pr.second, C))) return rc;
-        if ((rc = copy_out(pr.first, v.data(), C * 8))) return rc;
+        if ((rc = dev_out(pr.first, pr.second, C * 8))) return rc;
     }
     return PNS_OK;
 }
@@ -1814,22 +1879,16 @@ int pns_read_log(pns_ctx* ctx, int32_t* actions, int64_t* multiplicities, double
     if (rc) return rc;
     const size_t cnt = (size_t)ctx->num_chains * ctx->log_cap;
     if (actions) {
-        std::vector<int32_t> v;
-        if ((rc = d2h(v, ctx->log_action, cnt)) || (rc = copy_out(actions, v.data(), cnt * 4))) return rc;
+        if ((rc = dev_out(actions, ctx->log_action, cnt * 4))) return rc;
     }
     if (multiplicities) {
-        std::vector<int64_t> v;
-        if ((rc = d2h(v, ctx->log_M, cnt)) || (rc = copy_out(multiplicities, v.data(), cnt * 8))) return rc;
+        if ((rc = dev_out(multiplicities, ctx->log_M, cnt * 8))) return rc;
     }
     if (energies) {
-        std::vector<int64_t> v;
-        if ((rc = d2h(v, ctx->log_E, cnt))) return rc;
-        std::vector<double> e = energies_to_double(ctx, v);
-        if ((rc = copy_out(energies, e.data(), cnt * 8))) return rc;
+        if ((rc = energies_out(ctx, energies, ctx->log_E, cnt))) return rc;
     }
     if (p) {
-        std::vector<double> v;
-        if ((rc = d2h(v, ctx->log_p, cnt)) || (rc = copy_out(p, v.data(), cnt * 8))) return rc;
+        if ((rc = dev_out(p, ctx->log_p, cnt * 8))) return rc;
     }
     return PNS_OK;
 }
@@ -1843,12 +1902,10 @@ int pns_read_hist(pns_ctx* ctx, uint64_t* hist_weighted, uint64_t* hist_visits)
     if (rc) return rc;
     const size_t cnt = (size_t)1 << ctx->probs[0].N;
     if (hist_weighted) {
-        std::vector<uint64_t> v;
-        if ((rc = d2h(v, ctx->hist_w, cnt)) || (rc = copy_out(hist_weighted, v.data(), cnt * 8))) return rc;
+        if ((rc = dev_out(hist_weighted, ctx->hist_w, cnt * 8))) return rc;
     }
     if (hist_visits) {
-        std::vector<uint64_t> v;
-        if ((rc = d2h(v, ctx->hist_v, cnt)) || (rc = copy_out(hist_visits, v.data(), cnt * 8))) return rc;
+        if ((rc = dev_out(hist_visits, ctx->hist_v, cnt * 8))) return rc;
     }
     return PNS_OK;
 }
@@ -1880,20 +1937,13 @@ int pns_read_snapshots(pns_ctx* ctx, uint8_t* states, int64_t* multiplicities, d
     for (int32_t v : cnt) stored = std::min<int32_t>(stored, v);
     if (count) *count = stored;
     if (states) {
-        std::vector<uint8_t> xp;
-        if ((rc = d2h(xp, ctx->snap_x, (size_t)C * S * ctx->max_pitch))) return rc;
-        std::vector<uint8_t> xs = compact_rows(ctx, xp, ctx->max_pitch, S);
-        if ((rc = copy_out(states, xs.data(), xs.size()))) return rc;
+        if ((rc = rows_out(ctx, states, ctx->snap_x, 1, true, S, nullptr))) return rc;
     }
     if (multiplicities) {
-        std::vector<int64_t> v;
-        if ((rc = d2h(v, ctx->snap_M, (size_t)C * S)) || (rc = copy_out(multiplicities, v.data(), C * S * 8))) return rc;
+        if ((rc = dev_out(multiplicities, ctx->snap_M, C * S * 8))) return rc;
     }
     if (energies) {
-        std::vector<int64_t> v;
-        if ((rc = d2h(v, ctx->snap_E, (size_t)C * S))) return rc;
-        std::vector<double> e = energies_to_double(ctx, v);
-        if ((rc = copy_out(energies, e.data(), C * S * 8))) return rc;
+        if ((rc = energies_out(ctx, energies, ctx->snap_E, C * S))) return rc;
     }
     return PNS_OK;
 }
@@ -2131,9 +2181,7 @@ int pns_read_rb_weights(pns_ctx* ctx, double* log_w, double* snap_w, double* his
     if (rc) return rc;
     const int64_t C = ctx->num_chains;
     auto out = [&](double* dst, const double* src, size_t cnt) {
-        std::vector<double> v;
-        int r = d2h(v, src, cnt);
-        return r ? r : copy_out(dst, v.data(), cnt * 8);
+        return dev_out(dst, src, cnt * 8);
     };
     if (log_w && (rc = out(log_w, ctx->log_w, (size_t)C * ctx->log_cap))) return rc;
     if (snap_w && (rc = out(snap_w, ctx->snap_w, (size_t)C * ctx->snap_cap))) return rc;
@@ -2369,18 +2417,10 @@ int pns_read_best(pns_ctx* ctx, uint8_t* states, double* energies)
     if (rc) return rc;
     const int64_t C = ctx->num_chains;
     if (states) {
-        std::vector<uint8_t> xp;
-        if ((rc = d2h(xp, ctx->xbest, (size_t)ctx->fields))) return rc;
-        std::vector<uint8_t> xs((size_t)ctx->h_offsets.back());
-        for (int64_t c = 0; c < C; ++c)
-            std::memcpy(&xs[ctx->h_offsets[c]], &xp[ctx->h_foff[c]], ctx->probs[ctx->h_chain_problem[c]].N);
-        if ((rc = copy_out(states, xs.data(), xs.size()))) return rc;
+        if ((rc = rows_out(ctx, states, ctx->xbest, 1, false, 1, nullptr))) return rc;
     }
     if (energies) {
-        std::vector<int64_t> eb;
-        if ((rc = d2h(eb, ctx->Ebest, C))) return rc;
-        std::vector<double> e = energies_to_double(ctx, eb);
-        if ((rc = copy_out(energies, e.data(), C * 8))) return rc;
+        if ((rc = energies_out(ctx, energies, ctx->Ebest, C))) return rc;
     }
     return PNS_OK;
 }
@@ -2902,9 +2942,7 @@ int pns_cont_read(pns_cont* ctx, double* states, double* log_density, int64_t* L
     const size_t C = (size_t)ctx->C;
     int rc = PNS_OK;
     auto out64 = [&](void* dst, const void* src, size_t count) {
-        std::vector<int64_t> v;
-        int r = d2h(v, src, count);
-        return r ? r : copy_out(dst, v.data(), count * 8);
+        return dev_out(dst, src, count * 8);
     };
     if (states && (rc = out64(states, ctx->x, C * ctx->dim))) return rc;
     if (log_density && (rc = out64(log_density, ctx->lpx, C))) return rc;
@@ -2924,13 +2962,10 @@ int pns_cont_read_log(pns_cont* ctx, int32_t* actions, int64_t* multiplicities, 
     const size_t n = (size_t)ctx->C * (size_t)ctx->o.log_capacity;
     int rc = PNS_OK;
     if (actions) {
-        std::vector<int32_t> v;
-        if ((rc = d2h(v, ctx->log_action, n)) || (rc = copy_out(actions, v.data(), n * 4))) return rc;
+        if ((rc = dev_out(actions, ctx->log_action, n * 4))) return rc;
     }
     auto out64 = [&](void* dst, const void* src) {
-        std::vector<int64_t> v;
-        int r = d2h(v, src, n);
-        return r ? r : copy_out(dst, v.data(), n * 8);
+        return dev_out(dst, src, n * 8);
     };
     if (multiplicities && (rc = out64(multiplicities, ctx->log_M))) return rc;
     if (log_density && (rc = out64(log_density, ctx->log_lp))) return rc;
@@ -2945,9 +2980,7 @@ int pns_cont_read_sums(pns_cont* ctx, double* sums)
     if (!ctx || !sums) return fail(PNS_EINVAL, "NULL argument");
     HIP_TRY(hipStreamSynchronize(ctx->stream), "stream synchronize");
     const size_t n = (size_t)ctx->C * cont_sums_count(ctx);
-    std::vector<double> v;
-    int rc = d2h(v, ctx->sums, n);
-    return rc ? rc : copy_out(sums, v.data(), n * 8);
+    return dev_out(sums, ctx->sums, n * 8);
 }
 
 int pns_cont_clear_sums(pns_cont* ctx)
