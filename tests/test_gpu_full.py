@@ -7,7 +7,7 @@ import numpy as np
 import pytest
 
 from paper_2210_10513_amd import inputs
-from paper_2210_10513_amd.binding import Sampler
+from paper_2210_10513_amd.binding import BatchSampler, Sampler
 
 pytestmark = pytest.mark.gpu
 
@@ -164,3 +164,26 @@ def test_int32_rows_of_the_wide_window_tiles(N, tile):
         out.append(_state(s.run(120), log=True))
         s.close()
     _same(out[0], out[1])
+
+
+@pytest.mark.parametrize("mode,kind", [("rf", "i16"), ("basic", "f32"), ("unbiased_sys", "i32"), ("unbiased_rand", "i16")])
+def test_batch_on_merged_tiles_equals_single_problems(mode, kind):
+    """Problems of a batch that run on a larger problem's tile."""
+    sizes, chains = (30, 200, 300, 600, 900, 1500, 2500, 5000), 3
+    probs = []
+    for i, N in enumerate(sizes):
+        Q, beta, layout = _problem(kind, N)
+        probs.append(dict(Q=Q, beta=beta, layout=layout, num_chains=chains, subset_size=0 if mode == "rf" else max(2, N // 10)))
+    b = BatchSampler(probs, mode, seed=11, log_capacity=30)
+    b.run(30)
+    log, cur = b.read_log(), b.read_current()
+    for i, (N, pr) in enumerate(zip(sizes, probs)):
+        t = _step_tile(N)
+        s = Sampler(pr["Q"], pr["beta"], pr["subset_size"], mode, num_chains=chains, layout=pr["layout"], seed=11,
+                    chain_id_base=chains * i, block=t[0], groups=t[1], log_capacity=30).run(30)
+        _same({k: v[i] for k, v in log.items()}, s.read_log())
+        c = s.read_current()
+        for k in ("x", "E", "h"):
+            assert np.array_equal(cur[k][i], c[k]), (N, k)
+        s.close()
+    b.close()
