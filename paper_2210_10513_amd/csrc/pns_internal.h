@@ -83,6 +83,7 @@ struct StepArgs {
     int64_t orig_time;              // > 0: advance by this many original samples (RF, Basic)
     uint8_t* xbest;                 // [fields] best state X_max, or NULL
     int64_t* Ebest;                 // [C] its energy bits
+    int32_t share;                  // one-wave window chains per workgroup, or 0
 };
 
 struct InitArgs {

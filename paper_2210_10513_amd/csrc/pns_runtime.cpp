@@ -515,6 +515,7 @@ struct LaunchClass {
     std::vector<int32_t> chains;
     int32_t* d_list = nullptr;
     double cost = 0.0;  // estimated time of one step of every chain of the class
+    int32_t share = 0;  // one-wave window chains per workgroup (0: by their number)
 };
 
 // Side streams of a context with several launch classes.  HIP spreads a
@@ -793,6 +794,7 @@ struct pns_ctx {
         }
         StepArgs a = args(steps);
         a.orig_time = orig_time;
+        a.share = k.share;
         if (classes.size() > 1 || (int32_t)k.chains.size() != num_chains) a.chain_list = k.d_list;
         const int ki = prof_on && prof_active ? class_index(k) : -1;
         if (ki >= 0 && first) HIP_TRY(prof_record(ki, 0, st), "profile start event");
@@ -1266,6 +1268,16 @@ int create_impl(pns_ctx** out, std::vector<ProblemSpec>& specs, int32_t mode, co
                 ctx->hold_ticks = (uint64_t)khz / 5;  // kHz x 0.2 ms
         }
         // longest-processing-time-first packing of the classes onto the side streams
+        // Classes that together need more LDS than the chip has wait for room:
+        // pairs of one-wave chains (31 KB) leave less of it unused than fours
+        // (64 problems of N 258 .. 15351, 4096 chains, 100000 steps: 635 ms in
+        // pairs, 670 in fours, 665 alone; 32 problems whose 2048 chains all fit:
+        // fours 7.8 ms, pairs 8.4).
+        size_t lds = 0;
+        for (auto& k : ctx->classes)
+            if (k.flav == 5) lds += k.chains.size() * (size_t)(9216 + 6144 * (k.tile.block / 64));
+        if (lds > (size_t)256 * 160 * 1024)
+            for (auto& k : ctx->classes) k.share = 2;
         for (auto& k : ctx->classes) k.cost = step_time(k.flav, k.tile, (double)k.chains.size());
         std::vector<int32_t> order(ctx->classes.size());
         for (size_t i = 0; i < order.size(); ++i) order[i] = (int32_t)i;

@@ -756,7 +756,7 @@ template <typename QT, int W, int G, bool INSTR>
 hipError_t launch_one(int32_t grid, hipStream_t st, const StepArgs& a)
 {
     static_assert(W > 1 || kMaxShare * sizeof(Lds<W, G>) <= 65536, "LDS of a workgroup");
-    const int32_t share = W == 1 ? share_of(grid) : 1;
+    const int32_t share = W > 1 ? 1 : a.share > 0 ? (a.share < kMaxShare ? a.share : kMaxShare) : share_of(grid);
     hipLaunchKernelGGL((wave_kernel<QT, W, G, INSTR>), dim3((grid + share - 1) / share), dim3(64 * W * share),
                        share * sizeof(Lds<W, G>), st, a, grid, share);
     return hipGetLastError();
