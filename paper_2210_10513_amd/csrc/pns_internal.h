@@ -261,9 +261,10 @@ hipError_t launch_moments_prep_f64(const double* w, int64_t K, int64_t kpad, uin
                                    unsigned long long* maxbits, hipStream_t st);
 // G[0..n) *= 2^ilogb(max): undoes the weight scaling of launch_moments_prep_f64.
 hipError_t launch_moments_unscale(double* G, int64_t n, const unsigned long long* maxbits, hipStream_t st);
-// log Z by enumeration: `blocks` x 256 threads, thread t covers the states
-// with high bits t and all 2^lowbits low bits; part_* hold `blocks` pairs.
+// log Z by enumeration: logz_blocks blocks (and the assignments `count` of the
+// bits above a lane's own); part_* hold `blocks` pairs.
+int32_t logz_blocks(int32_t N, int64_t* count);
 hipError_t launch_logz(int32_t qtype, const void* Q, int32_t N, int32_t layout, double beta, double* part_max,
-                       double* part_sum, int32_t blocks, int32_t lowbits, int64_t nthreads, double* out, hipStream_t st);
+                       double* part_sum, int32_t blocks, double* out, hipStream_t st);
 
 }  // namespace pns

@@ -19,6 +19,7 @@
 #include <type_traits>
 
 #include "pns_internal.h"
+#include "pns_step.h"
 
 namespace pns {
 namespace {
@@ -524,71 +525,122 @@ struct Acc<float> {
     using type = double;
 };
 
-// Thread t enumerates the 2^lowbits states whose high bits are t, the low
-// bits in Gray-code order (one flip per state, energy updated by dE).
-// Writes the thread's (max, sum) of exp(-beta E - max) pairs, block-reduced.
-template <typename QT>
+// Lane l of a wave takes the assignment t = 64 u + l of the bits from 4 + MID
+// up and enumerates the 2^(4 + MID) states below it: E is linear in the low bits
+// but for their own pairs, so that a state is two additions, one product and
+// one exponential.  Bits of u are the wave's: their terms are added for set bits
+// only.  The (max, sum) of exp(-beta E - max) pairs are block-reduced.
+// Bound: FP64 issue, about 30 operations per state (16 states per pass in
+// registers).  A call at N = 20 took 280 us and at N = 30 300 ms (2^14 threads
+// walking a Gray code with the fields in scratch memory), now 55 us and 1.2 ms;
+// MID = 4 from 2^24 states on, where 2^16 lanes are left and the terms of u are
+// shared by 16 times the states.
+template <typename QT, int MID>
 __global__ __launch_bounds__(256) void logz_kernel(const QT* __restrict__ Q, int32_t N, int32_t layout, double beta,
-                                                   int32_t lowbits, int64_t nthreads, double* out_max, double* out_sum)
+                                                   int64_t count, double* out_max, double* out_sum)
 {
     using AT = typename Acc<QT>::type;
+    constexpr int L = 4 + MID;  // bits below the lane's six
     __shared__ AT W[32][32];
     __shared__ AT dq[32];
+    __shared__ double etab[64][2];
     __shared__ double smax[256], ssum[256];
     const int tid = threadIdx.x;
-    for (int e = tid; e < N * N; e += blockDim.x) {
-        const int i = e / N, j = e % N;
-        AT v;
-        if (i == j) {
-            v = (AT)Q[i * N + i];
-            dq[i] = v;
-            v = (AT)0;
-        } else if (layout == 0) {
-            v = (AT)Q[i * N + j] + (AT)Q[j * N + i];
-        } else {
-            v = i < j ? (AT)Q[i * N + j] : (AT)Q[j * N + i];
+    for (int e = tid; e < 32 * 32; e += blockDim.x) {
+        const int i = e / 32, j = e % 32;
+        AT v = (AT)0;
+        if (i < N && j < N) {
+            if (i == j) v = (AT)0;
+            else if (layout == 0) v = (AT)Q[i * N + j] + (AT)Q[j * N + i];
+            else v = i < j ? (AT)Q[i * N + j] : (AT)Q[j * N + i];
         }
         W[i][j] = v;
+        if (i == j) dq[i] = i < N ? (AT)Q[i * N + i] : (AT)0;
     }
+    for (int i = tid; i < 128; i += blockDim.x) etab[i >> 1][i & 1] = step::kExp2[i >> 1][i & 1];
     __syncthreads();
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + tid;
+    const int lane = tid & 63;
+    const int states = N < 4 ? 1 << N : 16;
+    // the lane's six bits: their pairs, and their terms in the lower bits
+    AT Elane = 0, fl[L];
+#pragma unroll
+    for (int j = 0; j < L; ++j) fl[j] = 0;
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+        if (!((lane >> i) & 1)) continue;
+#pragma unroll
+        for (int k = 0; k < i; ++k)
+            if ((lane >> k) & 1) Elane += W[L + i][L + k];
+#pragma unroll
+        for (int j = 0; j < L; ++j) fl[j] += W[L + i][j];
+    }
+    // pairs of the four lowest bits
+    AT pair[16];
+    pair[0] = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+#pragma unroll
+        for (int st = 0; st < (1 << j); ++st) {
+            AT p = pair[st];
+#pragma unroll
+            for (int k = 0; k < j; ++k)
+                if ((st >> k) & 1) p += W[j][k];
+            pair[st | (1 << j)] = p;
+        }
+    }
     double mx = -INFINITY, sm = 0.0;
-    if (t < nthreads) {
-        const uint64_t hi = (uint64_t)t << lowbits;
-        uint32_t x = 0;  // low bits
-        AT h[32];        // h_j = sum_{i != j} W_ij x_i over the whole state
-        AT E = 0;
-        for (int j = 0; j < N; ++j) {
-            AT acc = 0;
-            for (int i = 0; i < N; ++i)
-                if (i != j && ((hi >> i) & 1u)) acc += W[i][j];
-            h[j] = acc;
+    const int64_t waves = (int64_t)gridDim.x * (blockDim.x / 64);
+    for (int64_t u = (int64_t)blockIdx.x * (blockDim.x / 64) + __builtin_amdgcn_readfirstlane(tid >> 6); u * 64 < count; u += waves) {
+        AT g[L + 6], E = Elane;
+#pragma unroll
+        for (int j = 0; j < L + 6; ++j) g[j] = dq[j];
+        for (uint32_t m = (uint32_t)u; m; m &= m - 1) {
+            const int i = L + 6 + __builtin_ctz(m);
+            E += dq[i];
+            for (uint32_t r = m & (m - 1); r; r &= r - 1) E += W[i][L + 6 + __builtin_ctz(r)];
+#pragma unroll
+            for (int j = 0; j < L + 6; ++j) g[j] += W[i][j];
         }
-        for (int i = lowbits; i < N; ++i)
-            if ((hi >> i) & 1u) E += dq[i];
-        // E = sum_i d_i x_i + sum_{i<j} W_ij x_i x_j for the high bits alone
-        for (int i = lowbits; i < N; ++i) {
-            if (!((hi >> i) & 1u)) continue;
-            for (int j = i + 1; j < N; ++j)
-                if ((hi >> j) & 1u) E += W[i][j];
-        }
-        const uint64_t count = (uint64_t)1 << lowbits;
-        for (uint64_t g = 0; g < count; ++g) {
-            if (g > 0) {
-                const int c = __builtin_ctzll(g);
-                const bool on = (x >> c) & 1u;
-                const AT dE = on ? -(dq[c] + h[c]) : (dq[c] + h[c]);
-                E += dE;
-                x ^= 1u << c;
-                for (int j = 0; j < N; ++j)
-                    if (j != c) h[j] += on ? -W[c][j] : W[c][j];
+#pragma unroll
+        for (int i = 0; i < 6; ++i) E += (lane >> i) & 1 ? g[L + i] : (AT)0;
+#pragma unroll
+        for (int j = 0; j < L; ++j) g[j] += fl[j];
+        if (u * 64 + lane >= count) continue;
+#pragma unroll 1
+        for (int c = 0; c < (1 << MID); ++c) {
+            AT h[4], base = E;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) h[j] = g[j];
+#pragma unroll
+            for (int b = 0; b < MID; ++b) {
+                if (!((c >> b) & 1)) continue;
+                base += g[4 + b];
+#pragma unroll
+                for (int k = 0; k < b; ++k)
+                    if ((c >> k) & 1) base += W[4 + b][4 + k];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) h[j] += W[4 + b][j];
             }
-            const double v = -beta * (double)E;
-            if (v > mx) {
-                sm = sm * exp(mx - v) + 1.0;
-                mx = v;
-            } else {
-                sm += exp(v - mx);
+            AT e[16];
+            e[0] = base;
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int st = 0; st < (1 << j); ++st) e[st | (1 << j)] = e[st] + h[j];
+            double v[16], top = -INFINITY;
+#pragma unroll
+            for (int st = 0; st < 16; ++st) {
+                v[st] = st < states ? -beta * (double)(e[st] + pair[st]) : -INFINITY;
+                top = fmax(top, v[st]);
+            }
+            if (top > mx) {
+                sm *= exp(mx - top);
+                mx = top;
+            }
+#pragma unroll
+            for (int st = 0; st < 16; ++st) {
+                const double w = step::exp_nonpos(v[st] - mx, etab);
+                sm += st < states ? w : 0.0;
             }
         }
     }
@@ -769,18 +821,30 @@ hipError_t launch_moments_int(const uint8_t* X, int64_t ldx, const int64_t* m, i
     return hipGetLastError();
 }
 
-hipError_t launch_logz(int32_t qtype, const void* Q, int32_t N, int32_t layout, double beta, double* part_max,
-                       double* part_sum, int32_t blocks, int32_t lowbits, int64_t nthreads, double* out, hipStream_t st)
+// Assignments of the bits above a lane's own, and blocks of 256 lanes for them.
+int32_t logz_blocks(int32_t N, int64_t* count)
 {
-    if (qtype == Q_I16)
-        hipLaunchKernelGGL(logz_kernel<int16_t>, dim3(blocks), dim3(256), 0, st, reinterpret_cast<const int16_t*>(Q), N,
-                           layout, beta, lowbits, nthreads, part_max, part_sum);
-    else if (qtype == Q_I32)
-        hipLaunchKernelGGL(logz_kernel<int32_t>, dim3(blocks), dim3(256), 0, st, reinterpret_cast<const int32_t*>(Q), N,
-                           layout, beta, lowbits, nthreads, part_max, part_sum);
-    else
-        hipLaunchKernelGGL(logz_kernel<float>, dim3(blocks), dim3(256), 0, st, reinterpret_cast<const float*>(Q), N,
-                           layout, beta, lowbits, nthreads, part_max, part_sum);
+    const int32_t own = N >= 24 ? 8 : std::min(N, 4);
+    *count = (int64_t)1 << (N - own);
+    return (int32_t)std::min<int64_t>(4096, (*count + 255) / 256);
+}
+
+template <typename QT>
+void logz_typed(const void* Q, int32_t N, int32_t layout, double beta, double* pm, double* ps, hipStream_t st)
+{
+    int64_t count = 0;
+    const int32_t blocks = logz_blocks(N, &count);
+    const QT* q = reinterpret_cast<const QT*>(Q);
+    if (N >= 24) hipLaunchKernelGGL((logz_kernel<QT, 4>), dim3(blocks), dim3(256), 0, st, q, N, layout, beta, count, pm, ps);
+    else hipLaunchKernelGGL((logz_kernel<QT, 0>), dim3(blocks), dim3(256), 0, st, q, N, layout, beta, count, pm, ps);
+}
+
+hipError_t launch_logz(int32_t qtype, const void* Q, int32_t N, int32_t layout, double beta, double* part_max,
+                       double* part_sum, int32_t blocks, double* out, hipStream_t st)
+{
+    if (qtype == Q_I16) logz_typed<int16_t>(Q, N, layout, beta, part_max, part_sum, st);
+    else if (qtype == Q_I32) logz_typed<int32_t>(Q, N, layout, beta, part_max, part_sum, st);
+    else logz_typed<float>(Q, N, layout, beta, part_max, part_sum, st);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(logz_finish_kernel, dim3(1), dim3(256), 0, st, part_max, part_sum, blocks, out);

@@ -2307,23 +2307,20 @@ int pns_log_partition(const void* Q, int32_t N, int32_t dtype, int32_t layout, d
     std::vector<uint8_t> qh(qbytes);
     int rc = copy_in(qh.data(), Q, qbytes);
     if (rc) return rc;
-    const int32_t lowbits = std::max(std::min(N, 6), N - 14);
-    const int64_t nthreads = (int64_t)1 << (N - lowbits);
-    const int32_t blocks = (int32_t)((nthreads + 255) / 256);
-    uint8_t* dq = nullptr;
+    int64_t count = 0;
+    const int32_t blocks = logz_blocks(N, &count);
+    // one allocation: the blocks' pairs, the result, Q
     double* part = nullptr;
-    double* dout = nullptr;
     auto done = [&](int r) {
-        if (dq) (void)hipFree(dq);
         if (part) (void)hipFree(part);
-        if (dout) (void)hipFree(dout);
         return r;
     };
-    if ((rc = dev_alloc(&dq, qbytes)) || (rc = dev_alloc(&part, (size_t)2 * blocks)) || (rc = dev_alloc(&dout, 1)))
-        return done(rc);
+    if ((rc = dev_alloc(&part, (size_t)2 * blocks + 1 + (qbytes + 7) / 8))) return done(rc);
+    double* dout = part + (size_t)2 * blocks;
+    void* dq = dout + 1;
     hipError_t e = hipMemcpyAsync(dq, qh.data(), qbytes, hipMemcpyHostToDevice, st);
     if (e == hipSuccess)
-        e = launch_logz(dtype, dq, N, layout, beta, part, part + blocks, blocks, lowbits, nthreads, dout, st);
+        e = launch_logz(dtype, dq, N, layout, beta, part, part + blocks, blocks, dout, st);
     double v = 0.0;
     if (e == hipSuccess) e = hipMemcpyAsync(&v, dout, 8, hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);

@@ -1,0 +1,42 @@
+"""GPU test of log Z by enumeration at the edges of the kernel's split of the
+bits (4 or 8 per lane pass, 6 for the lanes, the rest for the waves), against a
+blocked FP64 enumeration."""
+import numpy as np
+import pytest
+
+from paper_2210_10513_amd import binding
+
+pytestmark = pytest.mark.gpu
+
+
+def _log_z(Q, beta, upper):
+    """FP64 (long double sums): states as (high, low) halves."""
+    N = Q.shape[0]
+    A = np.triu(Q, 1) if upper else np.triu(Q, 1) + np.tril(Q, -1).T
+    lo = min(N, 11)
+    X = lambda n: ((np.arange(1 << n)[:, None] >> np.arange(n)) & 1).astype(np.float64)
+    xl, xh = X(lo), X(N - lo)
+    d = np.diag(Q)
+    el = xl @ d[:lo] + ((xl @ A[:lo, :lo]) * xl).sum(1)
+    eh = xh @ d[lo:] + ((xh @ A[lo:, lo:]) * xh).sum(1)
+    cross = xh @ A[:lo, lo:].T
+    top, total = -np.inf, np.longdouble(0)
+    for i in range(0, len(xh), 256):
+        v = -beta * (eh[i:i + 256, None] + cross[i:i + 256] @ xl.T + el[None])
+        m = max(top, v.max())
+        total = total * np.exp(np.longdouble(top - m)) + np.exp(v - m).sum(dtype=np.longdouble)
+        top = m
+    return float(top + np.log(total))
+
+
+# relative rounding: energies of up to N^2 / 2 terms, weights within an ulp
+@pytest.mark.parametrize("dtype,upper", [(np.int16, False), (np.int32, True), (np.float32, False)])
+@pytest.mark.parametrize("N", [2, 3, 4, 9, 10, 11, 17, 23, 24, 25])
+def test_log_partition_over_the_split(dtype, upper, N):
+    rng = np.random.default_rng(N)
+    Q = rng.integers(-20, 21, (N, N)) if np.issubdtype(dtype, np.integer) else rng.standard_normal((N, N))
+    Q = (np.triu(Q) if upper else np.triu(Q) + np.triu(Q, 1).T).astype(dtype)
+    for beta in (0.05, 3.0):
+        got = binding.pns_log_partition(Q, beta, layout=binding.PNS_UPPER if upper else binding.PNS_SYMMETRIC)
+        want = _log_z(Q.astype(np.float64), beta, upper)
+        assert abs(got - want) <= 1e-13 * N * max(1.0, abs(want))
