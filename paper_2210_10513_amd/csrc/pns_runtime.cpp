@@ -641,7 +641,7 @@ struct pns_ctx {
     Problem* problems = nullptr;
     int32_t* chain_problem = nullptr;
     int64_t* foff = nullptr;
-    int64_t* offsets = nullptr;  // h_offsets
+    int64_t* offsets = nullptr;  // h_offsets, after foff
     int device = 0;              // the device of this memory
     std::mutex rows_mutex;       // of rows_ws: gathered rows on their way to host memory
     uint8_t* rows_ws = nullptr;
@@ -849,7 +849,7 @@ struct pns_ctx {
         if (graph) (void)hipGraphDestroy(graph);
         for (hipEvent_t ev : prof_ev)
             if (ev) (void)hipEventDestroy(ev);
-        void* ptrs[] = {problems, chain_problem, foff, offsets, rows_ws, beta, chain_id, x, h, fields_ws, rmem, E, L, sub, step, last_action, last_M,
+        void* ptrs[] = {problems, chain_problem, foff, rows_ws, beta, chain_id, x, h, fields_ws, rmem, E, L, sub, step, last_action, last_M,
                         last_E, counters, log_action, log_M, log_E, log_p, log_w, hist_w, hist_v, hist_rb,
                         snap_x, snap_M, snap_E, snap_w, snap_count};
         for (void* p : ptrs)
@@ -1176,8 +1176,8 @@ int create_impl(pns_ctx** out, std::vector<ProblemSpec>& specs, int32_t mode, co
     ALLOC(ctx->problems, Problem, specs.size());
     ALLOC(ctx->chain_problem, int32_t, C);
     if (hipGetDevice(&ctx->device) != hipSuccess) return fail_free(fail(PNS_EDEVICE, "no current device"));
-    ALLOC(ctx->foff, int64_t, C);
-    ALLOC(ctx->offsets, int64_t, C + 1);
+    ALLOC(ctx->foff, int64_t, 2 * C + 1);
+    ctx->offsets = ctx->foff + C;
     ALLOC(ctx->beta, double, C);
     ALLOC(ctx->chain_id, uint32_t, C);
     ALLOC(ctx->x, uint8_t, fields);
@@ -1229,8 +1229,9 @@ int create_impl(pns_ctx** out, std::vector<ProblemSpec>& specs, int32_t mode, co
     } while (0)
     H2D(ctx->problems, dev_probs.data(), dev_probs.size() * sizeof(Problem));
     H2D(ctx->chain_problem, ctx->h_chain_problem.data(), C * sizeof(int32_t));
-    H2D(ctx->offsets, ctx->h_offsets.data(), (C + 1) * sizeof(int64_t));
-    H2D(ctx->foff, ctx->h_foff.data(), C * sizeof(int64_t));
+    std::vector<int64_t> places(ctx->h_foff);
+    places.insert(places.end(), ctx->h_offsets.begin(), ctx->h_offsets.end());
+    H2D(ctx->foff, places.data(), places.size() * sizeof(int64_t));
     H2D(ctx->beta, betas.data(), C * sizeof(double));
     H2D(ctx->chain_id, cidv.data(), C * sizeof(uint32_t));
     H2D(ctx->L, Lv.data(), C * sizeof(int64_t));
