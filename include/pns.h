@@ -593,7 +593,7 @@ int pns_moments_f64(const uint8_t* X, int64_t ldx, const double* w, int64_t K, i
  *     otherwise): nothing is staged, and the call only queues work on
  *     `stream`;
  *   - the workspace (weight pieces, packed records, partial tiles) is a
- *     static 32 MiB array on each GPU, held until the process ends; a call
+ *     static 68 MiB array on each GPU, held until the process ends; a call
  *     whose workspace would exceed it is refused with PNS_EINVAL (about
  *     K * N / 8 bytes of packed records plus 16 KiB per 64 x 64 tile of the
  *     upper triangle; K = 131072 records of N = 512 fit);

@@ -10,8 +10,7 @@
 //   v_mfma_f32_16x16x32_bf16 with FP32 accumulation, each weight split into
 //   three bf16 pieces.
 // * log Z = log sum_x exp(-beta x^T Q x) by enumeration of all 2^N states
-//   (N <= 32) in Gray-code order with an incremental energy, FP64
-//   log-sum-exp.
+//   (N <= 32), 16 states of a lane at a time, FP64 log-sum-exp.
 #include <math.h>
 #include <stdint.h>
 
