@@ -67,26 +67,27 @@ os.environ["GPU_MAX_HW_QUEUES"] = _hw_queues_arg()
 HBM_PEAK_GBS = 8000.0
 
 
-def _kernel_sha(window: bool = False) -> str:
+def _kernel_sha(window: bool = False, full: bool = False) -> str:
     """sha256 prefix of a sampling kernel's sources: the step kernel's
-    (pns_step.h), or the window kernel's (pns_step.h, then pns_wave.h, which
-    includes it).  A committed counter row applies while it is unchanged."""
+    (pns_step.h), the window kernel's (pns_step.h, then pns_wave.h, which
+    includes it), or that of all bits and drawn subsets (pns_step.h, then
+    pns_full.h).  A committed counter row applies while it is unchanged."""
     import hashlib
     h = hashlib.sha256()
-    for name in ("pns_step.h", "pns_wave.h") if window else ("pns_step.h",):
+    for name in ("pns_step.h",) + (("pns_wave.h",) if window else ("pns_full.h",) if full else ()):
         h.update(open(os.path.join(ROOT, "paper_2210_10513_amd", "csrc", name), "rb").read())
     return h.hexdigest()[:16]
 
 
-def _measured_traffic(workload: str, chain_steps: int, window: bool = False):
-    """HBM bytes per launch of the step kernel (window: the window kernel)
+def _measured_traffic(workload: str, chain_steps: int, window: bool = False, full: bool = False):
+    """HBM bytes per launch of the step kernel (window, full: as _kernel_sha)
     from the committed rocprofv3 counter runs (profiles/hbm_traffic.txt), or
     None when no run matches the workload and launch length or the kernel's
     sources changed since."""
     path = os.path.join(ROOT, "profiles", "hbm_traffic.txt")
     if not os.path.exists(path):
         return None
-    sha = _kernel_sha(window)
+    sha = _kernel_sha(window, full)
     for line in open(path):
         f = line.split()
         if len(f) == 6 and not line.startswith("#") and f[0] == workload and int(f[1]) == chain_steps and f[2] == sha:
@@ -99,15 +100,15 @@ def _measured_traffic(workload: str, chain_steps: int, window: bool = False):
 VALU_ISSUE_PEAK = 256 * 4 * 2.4e9 / 4
 
 
-def _valu_per_chain_step(workload: str, tile, window: bool = False):
-    """VALU instructions (wave64) per chain step of the step kernel (window:
-    the window kernel) from the committed SQ counter runs
+def _valu_per_chain_step(workload: str, tile, window: bool = False, full: bool = False):
+    """VALU instructions (wave64) per chain step of the step kernel (window,
+    full: as _kernel_sha) from the committed SQ counter runs
     (profiles/valu_issue.txt), or None when no run matches the workload and
     tile (block, groups) or the kernel's sources changed since."""
     path = os.path.join(ROOT, "profiles", "valu_issue.txt")
     if not os.path.exists(path):
         return None
-    sha = _kernel_sha(window)
+    sha = _kernel_sha(window, full)
     for line in open(path):
         f = line.split()
         if (len(f) == 6 and not line.startswith("#") and f[0] == workload and f[1] == "%dx%d" % tuple(tile)
@@ -497,7 +498,7 @@ def _single_summary(name, args):
                       "chain_steps_per_step": wl["steps"], "tile": list(tile)},
            "flips_per_s": flips / sec, "effective_mh_steps_per_s": summ / sec, "records_per_s": recs / sec,
            "roofline": {"bound": "hbm", "achieved": k["GB_per_s"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                        "frac": k["hbm_frac"], "traffic": _measured_traffic(name, wl["steps"]),
+                        "frac": k["hbm_frac"], "traffic": _measured_traffic(name, wl["steps"], full=k["flavour"] in (6, 7)),
                         "bytes_per_flip": int(wl["Q"].shape[0] * wl["qbytes"]), "kernel_avg_ms": k["kernel_avg_ms"],
                         "bytes_per_launch": k["bytes_per_launch"]}}
     return out
@@ -743,12 +744,15 @@ def main():
         "records_per_s": recs / sec,
         "roofline": {"bound": "hbm", "achieved": k["GB_per_s"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": k["hbm_frac"],
-                     "traffic": _measured_traffic(args.workload, chain_steps) if args.steps >= 1 else None,
-                     "bytes_per_flip": bytes_per_flip, "kernel": "step_kernel",
+                     "traffic": (_measured_traffic(args.workload, chain_steps, full=k["flavour"] in (6, 7))
+                                 if args.steps >= 1 else None),
+                     "bytes_per_flip": bytes_per_flip,
+                     "kernel": {5: "wave_kernel", 6: "full_kernel", 7: "full_kernel"}.get(k["flavour"], "step_kernel"),
                      "kernel_avg_ms": k["kernel_avg_ms"], "bytes_per_launch": k["bytes_per_launch"],
                      "timing": "HIP events on the context's stream, every timed step"},
     }
-    vps = _valu_per_chain_step(args.workload, tile)
+    run_tile = tuple(int(v) for v in k["tile"].split("x"))
+    vps = _valu_per_chain_step(args.workload, run_tile, full=k["flavour"] in (6, 7))
     if vps is not None:
         # the bound of an L2-resident step: wave64 VALU issue (records = loop iterations)
         out["issue_roofline"] = {"bound": "alu", "achieved": vps * recs / sec, "peak": VALU_ISSUE_PEAK,

@@ -128,6 +128,14 @@ def test_rescaled_and_overflowing_weights_equal(kind, scale):
             _pair(Q, beta * scale, m, mode, layout, 4, lambda s: _state(s.run(80), log=True), log_capacity=80, L0=20)
 
 
+@pytest.mark.parametrize("N,n", [(30, 7), (900, 60), (3000, 200)])
+def test_more_draws_than_the_table_of_occurrences_numbers(N, n):
+    """One launch of more than 4095 draws: the keys' draw numbers run out and
+    the table is cleared."""
+    Q, beta, layout = _problem("i16", N)
+    _pair(Q, beta, n, "basic", layout, 2, lambda s: _state(s.run(9000)))
+
+
 def test_histogram_equal():
     for kind in ("i16", "f32"):
         Q, beta, layout = _problem(kind, 12)
