@@ -591,17 +591,16 @@ void merge_classes(std::vector<Exec>& ex, const std::vector<MergeItem>& items)
             for (size_t b = 0; b < gs.size(); ++b) {
                 const Tile t = gs[b].e.tile;
                 if (a == b || gs[b].e.flav != gs[a].e.flav || t.block * t.groups <= gs[a].e.tile.block * gs[a].e.tile.groups) continue;
-                bool fits = true;
-                for (size_t i : gs[a].items)
-                    fits = fits && items[i].N <= 4 * t.block * t.groups &&
-                           (gs[a].e.flav != 5 || window_slots_ok(items[i].N, items[i].n, t.block, t.groups));
-                if (!fits) continue;
                 std::vector<Group> v = gs;
                 v[b].chains += v[a].chains;
                 v[b].items.insert(v[b].items.end(), v[a].items.begin(), v[a].items.end());
                 v.erase(v.begin() + (ptrdiff_t)a);
                 const double T = step_of_all(v);
-                if (T < best) best = T, chosen = v;
+                bool fits = T < best;
+                for (size_t i : gs[a].items)
+                    fits = fits && items[i].N <= 4 * t.block * t.groups &&
+                           (gs[a].e.flav != 5 || window_slots_ok(items[i].N, items[i].n, t.block, t.groups));
+                if (fits) best = T, chosen = v;
             }
         }
         if (chosen.empty()) break;
