@@ -782,6 +782,19 @@ struct pns_ctx {
         return PNS_OK;
     }
 
+    // Exact-time Rejection-Free runs of 513 to 1024 bits and one to four chains
+    // per CU: the budget decision of a step, taken by one wave of the step kernel
+    // next to the others' choice, is serial work of a wave that holds the whole
+    // chain (4000 samples of 800 chains, int16 N = 900: 175 us, 214 on one wave;
+    // 4096 chains 430 and 339).
+    bool step_kernel_timed(const LaunchClass& k) const
+    {
+        const size_t C = k.chains.size();
+        if (k.flav != kFlavFull || C <= 256 || C > 1024) return false;
+        return (k.tile.block == 64 && (k.tile.groups == 4 || (k.tile.groups == 3 && htype == H_I32))) ||
+               (k.tile.block == 256 && k.tile.groups == 1);
+    }
+
     int launch_class(const LaunchClass& k, int64_t steps, hipStream_t st, int64_t orig_time = 0, bool first = true,
                      bool last = true)
     {
@@ -797,8 +810,11 @@ struct pns_ctx {
         if (classes.size() > 1 || (int32_t)k.chains.size() != num_chains) a.chain_list = k.d_list;
         const int ki = prof_on && prof_active ? class_index(k) : -1;
         if (ki >= 0 && first) HIP_TRY(prof_record(ki, 0, st), "profile start event");
-        hipError_t e = launch_steps(qtype, htype, k.flav, instrumented(), k.tile.block, k.tile.groups,
-                                    (int32_t)k.chains.size(), k.dyn, st, a);
+        Tile t = k.tile;
+        int32_t flav = k.flav;
+        size_t dyn = k.dyn;
+        if (orig_time > 0 && step_kernel_timed(k)) t = {256, 1}, flav = 0, dyn = dyn_lds(0, 1024);
+        hipError_t e = launch_steps(qtype, htype, flav, instrumented(), t.block, t.groups, (int32_t)k.chains.size(), dyn, st, a);
         if (e != hipSuccess) return hip_fail(e, "step kernel launch");
         if (ki >= 0) {
             ++prof_runs_now[ki];

@@ -195,3 +195,11 @@ def test_batch_on_merged_tiles_equals_single_problems(mode, kind):
             assert np.array_equal(cur[k][i], c[k]), (N, k)
         s.close()
     b.close()
+
+
+@pytest.mark.parametrize("kind", ["i16", "f32"])
+@pytest.mark.parametrize("N,chains", [(600, 257), (769, 257), (1000, 513), (1024, 1025)])
+def test_exact_time_runs_equal(kind, N, chains):
+    """Exact-time runs between sampling runs, where the two kernels take turns."""
+    Q, beta, layout = _problem(kind, N)
+    _pair(Q, beta, 0, "rf", layout, chains, lambda s: _state(s.run(20).run_original(70).run(5)))
