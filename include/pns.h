@@ -659,10 +659,12 @@ int pns_logz_grad(pns_ctx* ctx, int32_t problem, double beta, int32_t rb, double
 
 /*
  * log Z(Q, beta) = log sum_x exp(-beta x^T Q x) by enumeration of all 2^N
- * states on the device (Gray-code order, incremental energies: exact int64
- * for integer Q, FP64 for float Q; FP64 log-sum-exp).  Q [N][N] of `dtype`
- * in `layout`, host or device; *out is host or device.  Synchronises
- * `stream` (NULL: the default stream).
+ * states on the device (16 states of a lane at a time, energies in int64 for
+ * integer Q: exact, in FP64 for float Q; FP64 log-sum-exp).  Q [N][N] of
+ * `dtype` in `layout`, host or device; *out is host or device.  Float Q is not
+ * checked: an entry of +infinity takes the states that hold it out of the sum
+ * (beta > 0), and a NaN entry, one of -infinity, or an infinite one at beta = 0
+ * gives NaN.  Synchronises `stream` (NULL: the default stream).
  * Errors: PNS_EINVAL (N outside [1, 32], bad dtype or layout, beta < 0 or
  * not finite), PNS_ENOMEM, PNS_EDEVICE.
  */

@@ -545,6 +545,7 @@ __global__ __launch_bounds__(256) void logz_kernel(const QT* __restrict__ Q, int
     __shared__ double etab[64][2];
     __shared__ double smax[256], ssum[256];
     const int tid = threadIdx.x;
+    int odd = 0;  // an entry is infinite or NaN
     for (int e = tid; e < 32 * 32; e += blockDim.x) {
         const int i = e / 32, j = e % 32;
         AT v = (AT)0;
@@ -554,10 +555,11 @@ __global__ __launch_bounds__(256) void logz_kernel(const QT* __restrict__ Q, int
             else v = i < j ? (AT)Q[i * N + j] : (AT)Q[j * N + i];
         }
         W[i][j] = v;
-        if (i == j) dq[i] = i < N ? (AT)Q[i * N + i] : (AT)0;
+        if (i == j) v = dq[i] = i < N ? (AT)Q[i * N + i] : (AT)0;
+        if constexpr (std::is_floating_point<QT>::value) odd |= !isfinite(v);
     }
     for (int i = tid; i < 128; i += blockDim.x) etab[i >> 1][i & 1] = step::kExp2[i >> 1][i & 1];
-    __syncthreads();
+    odd = __syncthreads_or(odd);
     const int lane = tid & 63;
     const int states = N < 4 ? 1 << N : 16;
     // the lane's six bits: their pairs, and their terms in the lower bits
@@ -588,6 +590,7 @@ __global__ __launch_bounds__(256) void logz_kernel(const QT* __restrict__ Q, int
         }
     }
     double mx = -INFINITY, sm = 0.0;
+    bool bad = false;  // a state's -beta E is NaN or infinite
     const int64_t waves = (int64_t)gridDim.x * (blockDim.x / 64);
     for (int64_t u = (int64_t)blockIdx.x * (blockDim.x / 64) + __builtin_amdgcn_readfirstlane(tid >> 6); u * 64 < count; u += waves) {
         AT g[L + 6], E = Elane;
@@ -632,6 +635,11 @@ __global__ __launch_bounds__(256) void logz_kernel(const QT* __restrict__ Q, int
                 v[st] = st < states ? -beta * (double)(e[st] + pair[st]) : -INFINITY;
                 top = fmax(top, v[st]);
             }
+            // (the maximum passes over NaN, and the exponential takes it for 0)
+            if (odd) {
+#pragma unroll
+                for (int st = 0; st < 16; ++st) bad = bad || (st < states && !(v[st] < INFINITY));
+            }
             if (top > mx) {
                 sm *= exp(mx - top);
                 mx = top;
@@ -643,8 +651,8 @@ __global__ __launch_bounds__(256) void logz_kernel(const QT* __restrict__ Q, int
             }
         }
     }
-    smax[tid] = mx;
-    ssum[tid] = sm;
+    smax[tid] = bad ? INFINITY : mx;  // (infinity: the pair outlives the merges)
+    ssum[tid] = bad ? NAN : sm;
     __syncthreads();
     for (int st = 128; st > 0; st >>= 1) {
         if (tid < st) {

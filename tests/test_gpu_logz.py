@@ -40,3 +40,34 @@ def test_log_partition_over_the_split(dtype, upper, N):
         got = binding.pns_log_partition(Q, beta, layout=binding.PNS_UPPER if upper else binding.PNS_SYMMETRIC)
         want = _log_z(Q.astype(np.float64), beta, upper)
         assert abs(got - want) <= 1e-13 * N * max(1.0, abs(want))
+
+
+# the pair's bits among a lane's own, the lanes', the waves', and across them
+@pytest.mark.parametrize("N,i,j", [(1, 0, 0), (2, 0, 1), (5, 3, 4), (11, 0, 10), (12, 10, 11), (12, 11, 11), (25, 2, 9),
+                                   (25, 23, 24)])
+def test_log_partition_of_entries_that_are_not_finite(N, i, j):
+    """NaN in an entry in use comes through; states that hold a pair of weight
+    +infinity are out of the sum; entries that UPPER ignores do not matter."""
+    rng = np.random.default_rng(N)
+    U = np.triu(rng.standard_normal((N, N))).astype(np.float32)
+    for upper in (False, True):
+        layout = binding.PNS_UPPER if upper else binding.PNS_SYMMETRIC
+
+        def get(value, beta):
+            Q = U.copy() if upper else U + np.triu(U, 1).T
+            Q[i, j] = value
+            if not upper:
+                Q[j, i] = value
+            return binding.pns_log_partition(Q, beta, layout=layout)
+
+        assert np.isnan(get(np.nan, 0.7)) and np.isnan(get(np.nan, 0.0))
+        assert np.isnan(get(np.inf, 0.0)) and np.isnan(get(-np.inf, 0.7))
+        Q = (U.copy() if upper else U + np.triu(U, 1).T).astype(np.float64)
+        Q[i, j] = Q[j, i] = 1e30
+        want = _log_z(Q, 0.7, upper)
+        assert abs(get(np.inf, 0.7) - want) <= 1e-13 * N * max(1.0, abs(want))
+    if i != j:
+        Q = U.copy()
+        Q[j, i] = np.nan
+        assert binding.pns_log_partition(Q, 0.7, layout=binding.PNS_UPPER) == \
+            binding.pns_log_partition(U, 0.7, layout=binding.PNS_UPPER)
