@@ -298,15 +298,22 @@ static __device__ const double kExp2[64][2] = {
 // At most 0.512 ulp off over [-700, 0] (3e6 random arguments against 113-bit
 // values), where the series to degree 13 without a table, 7 more FP64
 // operations and 10 more constants, was 0.87 ulp off.
-// The constants are made opaque where they are used: scalar registers (the
-// first in a vector register: one scalar operand per instruction) that are not
-// moved to vector registers or kept across a loop.
+// HERE: the constants are made opaque where they are used: scalar registers
+// (the first in a vector register: one scalar operand per instruction) that are
+// not moved to vector registers or kept across a loop.  For the kernels of
+// straight-line weights; in the step kernel below, whose weights are formed
+// group by group, forming them at every use cost more than keeping them (float
+// random sets, N = 700, us per step: 64 chains 2.00 formed, 1.84 kept, 1.91 with
+// the library's exp; 2048 chains 4.4, 4.0 and 4.3).
+template <bool HERE = true>
 __device__ __forceinline__ double exp_nonpos(double l, const double (*tab)[2])
 {
     double c6 = 1.0 / 720.0, c5 = 1.0 / 120.0, c4 = 1.0 / 24.0, c3 = 1.0 / 6.0;
     double log2e = 0x1.71547652b82fep+6, ln2_hi = -0x1.62e42fee00000p-7, ln2_lo = -0x1.a39ef35793c76p-39;
-    asm("" : "+v"(c6), "+s"(c5), "+s"(c4), "+s"(c3));
-    asm("" : "+s"(log2e), "+s"(ln2_hi), "+s"(ln2_lo));
+    if constexpr (HERE) {
+        asm("" : "+v"(c6), "+s"(c5), "+s"(c4), "+s"(c3));
+        asm("" : "+s"(log2e), "+s"(ln2_hi), "+s"(ln2_lo));
+    }
     l = fmax(l, -746.0);
     const double k = rint(l * log2e);
     const double r = fma(k, ln2_lo, fma(k, ln2_hi, l));
@@ -473,7 +480,8 @@ void step_kernel(const StepArgs a)
     __shared__ uint32_t hist_idx;
     __shared__ double tab_lo[kInt ? 2 * kTabLo : 1];
     __shared__ double tab_hi[kInt ? kTabHi : 1];
-    __shared__ double etab[kInt ? 1 : 64][2];
+    constexpr bool kExpTab = !kInt && (FLAV == FLAV_ALL || FLAV == FLAV_DRAWN);
+    __shared__ double etab[kExpTab ? 64 : 1][2];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -532,7 +540,7 @@ void step_kernel(const StepArgs a)
             else if (i < 2 * kTabLo) tab_lo[i] = 0.0;
             else tab_hi[i - 2 * kTabLo] = exp(-beta * (double)(kTabLo * (i - 2 * kTabLo)));
         }
-    } else {
+    } else if constexpr (kExpTab) {
         for (int i = tid; i < 128; i += BLOCK) etab[i >> 1][i & 1] = kExp2[i >> 1][i & 1];
     }
 
@@ -741,6 +749,15 @@ void step_kernel(const StepArgs a)
                 return dg[i % F];
             }
         };
+        // Float weights.  All bits and drawn subsets: the table exponential, as in
+        // the kernel that runs them by default, whose records are the same.  A
+        // window's four weights of a lane are one serial chain in which the table's
+        // read waits: the library's exp (N = 150, 800 chains 2.00 us per step with
+        // it, 2.09 with the table; N = 8000, n = 2000, logged, 64 chains 4.06 and 4.70).
+        auto exp_of = [&](double l, double shift) -> double {
+            if constexpr (kExpTab) return exp_nonpos<false>(shift == 0.0 ? l : l - shift, etab);
+            else return shift == 0.0 ? exp(l) : exp(l - shift);
+        };
         auto member_weight = [&](int i, double shift) -> double {
             const QW di = diag_of(i);
             if constexpr (kInt) {
@@ -756,7 +773,7 @@ void step_kernel(const StepArgs a)
             } else {
                 double l = -beta * delta_f64(di, h[i], s, (xb >> i) & 1u);
                 l = l < 0.0 ? l : 0.0;
-                return exp_nonpos(shift == 0.0 ? l : l - shift, etab);
+                return exp_of(l, shift);
             }
         };
         double w[kKeepW || kTwo ? 4 : 1];  // weights of the lane's four bits (compact: in group gw; two-group: ga)
@@ -805,7 +822,7 @@ void step_kernel(const StepArgs a)
                     } else {
                         double l = -beta * delta_f64(d4.v[v], h4[v], s, (x4 >> v) & 1u);
                         l = l < 0.0 ? l : 0.0;
-                        wv = exp_nonpos(shift == 0.0 ? l : l - shift, etab);
+                        wv = exp_of(l, shift);
                     }
                     w4[v] = ((mg >> v) & 1u) ? wv : 0.0;
                 }
@@ -851,7 +868,7 @@ void step_kernel(const StepArgs a)
                 } else {
                     double l = -beta * delta_f64(d4.v[v], h4[v], s, (x4 >> v) & 1u);
                     l = l < 0.0 ? l : 0.0;
-                    wv = exp_nonpos(shift == 0.0 ? l : l - shift, etab);
+                    wv = exp_of(l, shift);
                 }
                 w4[v] = ((mg >> v) & 1u) ? wv : 0.0;
             }
