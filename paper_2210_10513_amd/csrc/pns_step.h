@@ -303,8 +303,8 @@ static __device__ const double kExp2[64][2] = {
 // not moved to vector registers or kept across a loop.  For the kernels of
 // straight-line weights; in the step kernel below, whose weights are formed
 // group by group, forming them at every use cost more than keeping them (float
-// random sets, N = 700, us per step: 64 chains 2.00 formed, 1.84 kept, 1.91 with
-// the library's exp; 2048 chains 4.4, 4.0 and 4.3).
+// random sets, N = 700, n = 64, us per step: 64 chains 2.02 formed, 1.84 kept,
+// 1.93 with the library's exp; 2048 chains 5.0, 4.7 and 5.1).
 template <bool HERE = true>
 __device__ __forceinline__ double exp_nonpos(double l, const double (*tab)[2])
 {
@@ -752,8 +752,8 @@ void step_kernel(const StepArgs a)
         // Float weights.  All bits and drawn subsets: the table exponential, as in
         // the kernel that runs them by default, whose records are the same.  A
         // window's four weights of a lane are one serial chain in which the table's
-        // read waits: the library's exp (N = 150, 800 chains 2.00 us per step with
-        // it, 2.09 with the table; N = 8000, n = 2000, logged, 64 chains 4.06 and 4.70).
+        // read waits: the library's exp (N = 150, n = 16, 800 chains 1.99 us per step
+        // with it, 2.13 with the table; N = 8000, n = 2000, logged, 64 chains 4.06 and 4.70).
         auto exp_of = [&](double l, double shift) -> double {
             if constexpr (kExpTab) return exp_nonpos<false>(shift == 0.0 ? l : l - shift, etab);
             else return shift == 0.0 ? exp(l) : exp(l - shift);
