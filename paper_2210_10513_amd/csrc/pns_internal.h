@@ -188,6 +188,7 @@ struct RowGather {
     const int32_t* chain_problem;
     const Problem* problems;
     int64_t pitch, per, row0;
+    int64_t first = 0;              // row of the launch's first workgroup, from row0
 };
 hipError_t launch_gather_rows(int32_t elem, int64_t rows, hipStream_t stream, const RowGather& args);
 

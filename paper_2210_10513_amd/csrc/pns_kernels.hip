@@ -3,6 +3,7 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "pns_internal.h"
@@ -321,7 +322,7 @@ __global__ void fill64_kernel(int64_t* p, int64_t count, int64_t value)
 template <typename T>
 __global__ void gather_rows_kernel(const RowGather a)
 {
-    const int64_t row = a.row0 + blockIdx.x;
+    const int64_t row = a.row0 + a.first + blockIdx.x;
     const int64_t c = row / a.per;
     const int64_t r = row - c * a.per;
     const int32_t N = a.problems[a.chain_problem[c]].N;
@@ -481,13 +482,19 @@ hipError_t launch_hold(uint64_t ticks, hipStream_t st)
 
 hipError_t launch_gather_rows(int32_t elem, int64_t rows, hipStream_t stream, const RowGather& a)
 {
-    if (rows <= 0) return hipSuccess;
-    const dim3 grid((unsigned)rows), block(256);
-    if (elem == 1) hipLaunchKernelGGL(gather_rows_kernel<uint8_t>, grid, block, 0, stream, a);
-    else if (elem == 4) hipLaunchKernelGGL(gather_rows_kernel<uint32_t>, grid, block, 0, stream, a);
-    else if (elem == 8) hipLaunchKernelGGL(gather_rows_kernel<uint64_t>, grid, block, 0, stream, a);
-    else return hipErrorInvalidValue;
-    return hipGetLastError();
+    // (a launch holds fewer than 2^32 threads: 2^23 rows of 256 at a time)
+    constexpr int64_t kMost = (int64_t)1 << 23;
+    RowGather p = a;
+    for (p.first = 0; p.first < rows; p.first += kMost) {
+        const dim3 grid((unsigned)std::min(rows - p.first, kMost)), block(256);
+        if (elem == 1) hipLaunchKernelGGL(gather_rows_kernel<uint8_t>, grid, block, 0, stream, p);
+        else if (elem == 4) hipLaunchKernelGGL(gather_rows_kernel<uint32_t>, grid, block, 0, stream, p);
+        else if (elem == 8) hipLaunchKernelGGL(gather_rows_kernel<uint64_t>, grid, block, 0, stream, p);
+        else return hipErrorInvalidValue;
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_fill64(void* p, int64_t count, int64_t value, hipStream_t stream)

@@ -66,3 +66,25 @@ def test_batch_rows_and_snapshots():
             assert np.array_equal(_energies(Q, snap), es[row])
             at, row = at + 3 * N, row + 1
     s.close()
+
+
+# more rows than one launch of a workgroup per row holds (2^32 threads), of a
+# size that a piece for host memory holds too (N = 1) or not
+@pytest.mark.parametrize("N", [1, 3])
+def test_reads_of_more_rows_than_one_launch_holds(N):
+    chains, keep = 4200, 4000
+    assert chains * keep > 2**24
+    Q = inputs.symmetric_int(N, -50, 50, np.int16, seed=N)
+    s = Sampler(Q, 0.02, 0, "rf", num_chains=chains, seed=5, init="random", snapshot_every=1, snapshot_capacity=keep)
+    s.run(keep)
+    xd = torch.full((chains, keep, N), 9, dtype=torch.uint8, device="cuda")
+    ed = torch.zeros((chains, keep), dtype=torch.float64, device="cuda")
+    binding.pns_read_snapshots(s.ctx, xd, None, ed)
+    Qd = torch.from_numpy(Q.astype(np.float64)).cuda()
+    for part in range(0, chains, 600):
+        x = xd[part:part + 600].double()
+        assert bool(((x @ Qd * x).sum(-1) == ed[part:part + 600]).all())
+    xh = np.zeros((chains, keep, N), np.uint8)
+    binding.pns_read_snapshots(s.ctx, xh, None, None)
+    assert np.array_equal(xd.cpu().numpy(), xh)
+    s.close()
