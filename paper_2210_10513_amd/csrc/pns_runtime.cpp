@@ -318,21 +318,73 @@ Tile default_tile_for(int32_t mode, int32_t N, int32_t n, int32_t qtype, int32_t
 // chain, where the step kernel's workgroups no longer share the chip in one
 // round (chains, step / window kernel: N = 700 4096 8.7 / 5.4; N = 1500 768 2.26 /
 // 2.27, 1024 4.2 / 2.3; N = 3000 512 2.5 / 2.7, 768 4.7 / 2.9; N = 8000 768 4.0 /
-// 3.8, 1024 6.8 / 4.3), and at all counts up to 512 bits (64 chains 1.8 / 1.5).
-// The step kernel stays where it is the faster one: int64 fields up to 1024
-// bits (256 chains of N = 1000: 1.9 against 2.3) and random sets of int64
-// fields (2.2 against 2.8), random sets of floats above 512 up to 1024 bits
-// (1024 chains of N = 1000: 2.7 against 3.3), and drawn subsets of floats above
-// 8192 bits, whose 32 fields per lane spill registers (12.5 against 13.4).
+// 3.8, 1024 6.8 / 4.3), and at all counts up to 512 bits (64 chains 1.8 / 1.5),
+// but for one-group problems of more chains than the chip holds of the window
+// kernel's (N = 150, n = 16: 2048 chains 2.3 / 1.9, 2560 2.6 / 3.0).
 struct Exec {
     Tile tile;
     int32_t flav;
 };
 
-Exec exec_of(Tile tile, int32_t flav, bool asked, int32_t N, int32_t n, int32_t qtype, int32_t htype, int32_t mode, bool hist,
-             int64_t chains)
+// Where the step kernel is the faster one of all-bits and drawn-subset runs.  It
+// weighs the four-bit groups that hold a member, where the kernel of pns_full.h
+// weighs every bit of the tile; and at some chain counts its workgroups fill the
+// chip in as many rounds.  us per step, step / full kernel:
+//   * int64 fields up to 1024 bits without a drawn subset (256 chains of N =
+//     1000 1.9 / 2.3) and random sets of int64 fields (2.2 / 2.8).
+//   * Rejection-Free int32 fields of 769 to 1024 bits at two to three chains per
+//     CU, 32-bit entries to four (N = 900, 600 chains, int16 1.51 / 1.60, int32 1.52 /
+//     1.67; 1024 chains, int32 N = 800 1.73 / 1.80, int16 N = 1024 1.74 / 1.64).
+//   * drawn subsets of floats above 8192 bits, whose 32 fields per lane spill
+//     registers (12.5 / 13.4), and the smallest ones of 769 to 2048 bits at two to
+//     three chains per CU (N = 1030, 600 chains, n = 2 3.75 / 3.92, n = 8 4.03 /
+//     3.96).
+//   * random sets, which are not drawn in each step: floats of 513 to 1024 bits,
+//     where an exponential per bit is never won back (1024 chains of N = 1000 2.7 /
+//     3.3), and small sets of others (N = 8000, 64 chains, n = 4 2.9 / 4.2, n = 64
+//     4.3 / 4.3, n = 256 5.3 / 4.4; N = 3500, 256 chains, n = 16 2.8 / 3.4, n = 128
+//     3.5 / 3.4; N = 1500, n = 16, 64 chains 2.8 / 2.3, 600 3.2 / 4.0, 2048 9.7 /
+//     10.6); integers of about 1000 bits up to four chains per CU (int32 N =
+//     1024, n = 192, 1 chain 1.67 / 1.85, 300 1.84 / 2.08, 700 1.99 / 2.30) and, with outputs of
+//     every step, of 1025 to 2048 (N = 1500, 300 chains 4.04 / 4.45).
+bool step_kernel_faster(bool drawn, bool random_sets, bool instr, int32_t N, int32_t n, int32_t qtype, int32_t htype,
+                        int64_t chains)
 {
-    const bool random_sets = mode == PNS_MODE_UNBIASED_RAND;
+    if (htype == H_I64) return drawn ? random_sets : N <= 1024;
+    const bool two_to_three = chains > 512 && chains <= 768;  // chains per CU
+    const bool i32 = htype == H_I32 && qtype == Q_I32;
+    if (!drawn) return htype == H_I32 && !instr && N > 768 && N <= 1024 && chains > 512 && chains <= (i32 ? 1024 : 768);
+    if (htype == H_I32) {
+        if (!random_sets || chains > 1024) return false;
+        if (instr) return N > 1024 && N <= 2048 && chains > 256 && chains <= 768;
+        if (N > 1024) return false;
+        const int32_t most = N > 928 ? 512 : 200;
+        if (chains <= 256) return i32 && (chains <= 16 ? N > 768 && n < most : N > 896 && n < std::min(most, 256));
+        if (chains <= 512) return N > 640 && n < (N > 768 ? most : 16);
+        return N > 768 && (two_to_three && N > 840 ? true : n >= 48 && (n < 256 || !two_to_three));
+    }
+    if (N > 8192) return true;
+    if (!random_sets) return !instr && N > 768 && N <= 2048 && n < 8 && two_to_three;
+    if (N <= 256) return n < 4 && chains > 3072;
+    if (N <= 512) return chains > 1024 ? n < 32 : (chains > 256 && chains <= 512) || (n < 8 && !instr);
+    if (N <= 1024) return true;
+    if (N <= 2048) {
+        if (chains <= 256) return n < 8;
+        if (chains <= 512) return instr || n < 64 || N <= 1088;
+        // (three workgroups of the step kernel to a CU, four of the other: by
+        // rounds of the chip; N = 1400, n = 128: 1024 chains 6.6 / 5.9, 1536 7.6 /
+        // 8.0, 2048 10.9 / 10.6)
+        const bool fewer_rounds = (chains + 1023) / 1024 < (chains + 767) / 768;
+        return !fewer_rounds || n * (N > 1088 ? 4 : 1) < (chains <= 1024 ? 128 : 256);
+    }
+    if (N <= 4096) return chains <= (N <= 3072 ? 256 : 512) && n < 96;
+    return n < (N <= 6144 ? 64 : 96);
+}
+
+// (instr: outputs of every step or snapshots, or an optimization run)
+Exec exec_of(Tile tile, int32_t flav, bool asked, int32_t N, int32_t n, int32_t qtype, int32_t htype, int32_t mode, bool hist,
+             bool instr, int64_t chains)
+{
     if (asked || flav == 5) return {tile, flav};
     if (flav != 0 && flav != 2) {
         if (mode != PNS_MODE_UNBIASED_SYS || hist) return {tile, flav};
@@ -342,15 +394,16 @@ Exec exec_of(Tile tile, int32_t flav, bool asked, int32_t N, int32_t n, int32_t 
                        : N <= 4096 ? Tile{64, 16}
                        : N <= 6144 ? Tile{64, 24}
                                    : Tile{128, 16};
-        const int64_t most = N <= 512 ? 0 : N <= 1024 ? 1024 : N > 2048 && N <= 4096 ? 512 : 768;
-        if (N <= 8192 && chains > most && have_wave_tile(qtype, htype, t.block, t.groups) && window_slots_ok(N, n, t.block, t.groups))
+        const int64_t above = N <= 512 ? 0 : N <= 1024 ? 1024 : N > 2048 && N <= 4096 ? 512 : 768;
+        const int64_t most = N <= 256 ? 2048 : INT64_MAX;
+        if (N <= 8192 && chains > above && chains <= most && have_wave_tile(qtype, htype, t.block, t.groups) &&
+            window_slots_ok(N, n, t.block, t.groups))
             return {t, 5};
         return {tile, flav};
     }
     const bool drawn = flav == 2, few = chains <= 512;
     const bool f64 = htype == H_F64, i64 = htype == H_I64;
-    if (i64 && (drawn ? random_sets : N <= 1024)) return {tile, flav};
-    if (f64 && drawn && (N > 8192 || (random_sets && N > 512 && N <= 1024))) return {tile, flav};
+    if (step_kernel_faster(drawn, mode == PNS_MODE_UNBIASED_RAND, instr, N, n, qtype, htype, chains)) return {tile, flav};
     Tile t{512, 8};
     if (N <= 256) t = {64, 1};
     else if (N <= 512) t = i64 || (f64 && few) ? Tile{128, 1} : Tile{64, 2};
@@ -1104,11 +1157,12 @@ int create_impl(pns_ctx** out, std::vector<ProblemSpec>& specs, int32_t mode, co
     for (size_t p = 0; p < specs.size(); ++p)
         if (flav[p] == 3 && specs[p].tile.groups >= 2 && tile_has4.count({specs[p].tile.block, specs[p].tile.groups}))
             flav[p] = 4;
+    const bool instr = o.log_capacity > 0 || o.hist || o.snapshot_every > 0;
     std::vector<Exec> execs;
     std::vector<MergeItem> items;
     for (size_t p = 0; p < specs.size(); ++p) {
         const ProblemSpec& S = specs[p];
-        execs.push_back(exec_of(S.tile, flav[p], S.asked, S.N, S.n, qtype, htype, mode, o.hist, total_chains));
+        execs.push_back(exec_of(S.tile, flav[p], S.asked, S.N, S.n, qtype, htype, mode, o.hist, instr, total_chains));
         items.push_back({S.N, S.n, S.chains, S.asked});
     }
     merge_classes(execs, items);
@@ -1412,7 +1466,7 @@ int reconfigure(pns_ctx* ctx, Tile t, int32_t n)
     D.s = R.s;
     D.qtype = ctx->qtype;
     HIP_TRY(hipMemcpy(ctx->problems, &D, sizeof(Problem), hipMemcpyHostToDevice), "reconfigure");
-    R.exec = exec_of(t, R.flav, false, R.N, R.n, ctx->qtype, ctx->htype, ctx->mode, false, ctx->num_chains);
+    R.exec = exec_of(t, R.flav, false, R.N, R.n, ctx->qtype, ctx->htype, ctx->mode, false, false, ctx->num_chains);
     LaunchClass& K = ctx->classes[0];
     K.tile = R.exec.tile;
     K.flav = R.exec.flav;
@@ -2487,7 +2541,8 @@ int pns_optimize(pns_ctx* ctx, int64_t steps, double temperature)
             const int32_t flav = (ctx->mode != PNS_MODE_RF && R.n < R.N) ? 2 : 0;
             // (a window-kernel tile runs the optimization on the table's)
             const Tile t = have_tile(ctx->qtype, ctx->htype, R.tile.block, R.tile.groups) ? R.tile : default_tile(R.N);
-            const Exec x = exec_of(t, flav, R.asked, R.N, R.n, ctx->qtype, ctx->htype, PNS_MODE_BASIC, false, ctx->num_chains);
+            const Exec x = exec_of(t, flav, R.asked, R.N, R.n, ctx->qtype, ctx->htype, PNS_MODE_BASIC, false, true,
+                                   ctx->num_chains);
             const auto key = std::make_pair(std::make_pair(x.tile.block, x.tile.groups), x.flav);
             if (!class_of.count(key)) {
                 class_of[key] = ctx->opt_classes.size();
