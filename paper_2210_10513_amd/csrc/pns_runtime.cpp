@@ -345,8 +345,8 @@ struct Exec {
 //     4.3 / 4.3, n = 256 5.3 / 4.4; N = 3500, 256 chains, n = 16 2.8 / 3.4, n = 128
 //     3.5 / 3.4; N = 1500, n = 16, 64 chains 2.8 / 2.3, 600 3.2 / 4.0, 2048 9.7 /
 //     10.6); integers of about 1000 bits up to four chains per CU (int32 N =
-//     1024, n = 192, 1 chain 1.67 / 1.85, 300 1.84 / 2.08, 700 1.99 / 2.30) and, with outputs of
-//     every step, of 1025 to 2048 (N = 1500, 300 chains 4.04 / 4.45).
+//     1024: n = 192, 300 chains 1.84 / 2.08; n = 300, 700 chains 1.99 / 2.30) and,
+//     with outputs of every step, of 1025 to 2048 (N = 1500, 300 chains 4.04 / 4.45).
 bool step_kernel_faster(bool drawn, bool random_sets, bool instr, int32_t N, int32_t n, int32_t qtype, int32_t htype,
                         int64_t chains)
 {
@@ -569,6 +569,7 @@ struct LaunchClass {
     int32_t* d_list = nullptr;
     double cost = 0.0;  // estimated time of one step of every chain of the class
     int32_t share = 0;  // one-wave window chains per workgroup (0: by their number)
+    int32_t n_max = 0;  // largest subset
 };
 
 // Side streams of a context with several launch classes.  HIP spreads a
@@ -835,17 +836,38 @@ struct pns_ctx {
         return PNS_OK;
     }
 
-    // Exact-time Rejection-Free runs of 513 to 1024 bits and one to four chains
-    // per CU: the budget decision of a step, taken by one wave of the step kernel
-    // next to the others' choice, is serial work of a wave that holds the whole
-    // chain (4000 samples of 800 chains, int16 N = 900: 175 us, 214 on one wave;
-    // 4096 chains 430 and 339).
-    bool step_kernel_timed(const LaunchClass& k) const
+    // The kernel of a class's exact-time runs.  The budget decision of a step is
+    // serial work that the kernel of pns_full.h does on a wave which holds the
+    // chain or much of it, the step kernel on one wave next to the others' choice;
+    // the step kernel is the faster one (ratios of its time to the other's) for
+    //   * Rejection-Free runs of 513 to 1024 bits at one to four chains per CU (4000
+    //     samples of 800 chains, int16 N = 900: 175 us, 214 on one wave; 4096 chains
+    //     430 and 339), and of int64 fields of 1025 to 2048 bits at two to three (N =
+    //     1030, 600 chains 0.92);
+    //   * drawn subsets of int64 fields up to 1024 bits (N = 700, n = 64: 64 chains
+    //     0.93, 800 0.85, 2048 0.90);
+    //   * the smallest drawn subsets of floats: of 513 to 2048 bits at one to three
+    //     chains per CU, four where one wave holds the chain (N = 1500, 600 chains,
+    //     n = 4 0.86, n = 8 0.92, n = 16 1.0; N = 700, 300 chains, n = 4 0.91, n = 16
+    //     1.03; N = 900, 1024 chains, n = 4 0.94), and of 6145 to 8192 (N = 6200, n = 4
+    //     0.94, n = 8 0.99).
+    Exec timed_exec(const LaunchClass& k) const
     {
         const size_t C = k.chains.size();
-        if (k.flav != kFlavFull || C <= 256 || C > 1024) return false;
-        return (k.tile.block == 64 && (k.tile.groups == 4 || (k.tile.groups == 3 && htype == H_I32))) ||
-               (k.tile.block == 256 && k.tile.groups == 1);
+        const Tile t = k.tile;
+        const int32_t bits = 4 * t.block * t.groups;
+        if (k.flav == kFlavFull && C > 256 && C <= 1024) {
+            if ((t.block == 64 && (t.groups == 4 || (t.groups == 3 && htype == H_I32))) || (t.block == 256 && t.groups == 1))
+                return {{256, 1}, 0};
+            if (htype == H_I64 && t.block == 256 && t.groups == 2 && C <= 768) return {t, 0};
+        }
+        if (k.flav == kFlavDraw && htype == H_I64 && bits <= 1024) return {t, 2};
+        if (k.flav == kFlavDraw && htype == H_F64) {
+            const bool one_wave = t.block == 64;
+            if (bits >= 1024 && bits <= 2048 && k.n_max < 16 && C > 256 && C <= (one_wave ? 1024 : 768)) return {default_tile(bits), 2};
+            if (t.block == 512 && t.groups == 4 && k.n_max < 8) return {t, 2};
+        }
+        return {t, k.flav};
     }
 
     int launch_class(const LaunchClass& k, int64_t steps, hipStream_t st, int64_t orig_time = 0, bool first = true,
@@ -863,11 +885,10 @@ struct pns_ctx {
         if (classes.size() > 1 || (int32_t)k.chains.size() != num_chains) a.chain_list = k.d_list;
         const int ki = prof_on && prof_active ? class_index(k) : -1;
         if (ki >= 0 && first) HIP_TRY(prof_record(ki, 0, st), "profile start event");
-        Tile t = k.tile;
-        int32_t flav = k.flav;
-        size_t dyn = k.dyn;
-        if (orig_time > 0 && step_kernel_timed(k)) t = {256, 1}, flav = 0, dyn = dyn_lds(0, 1024);
-        hipError_t e = launch_steps(qtype, htype, flav, instrumented(), t.block, t.groups, (int32_t)k.chains.size(), dyn, st, a);
+        const Exec x = orig_time > 0 ? timed_exec(k) : Exec{k.tile, k.flav};
+        const size_t dyn = x.flav == k.flav ? k.dyn : dyn_lds(x.flav, 4 * (int64_t)x.tile.block * x.tile.groups);
+        hipError_t e = launch_steps(qtype, htype, x.flav, instrumented(), x.tile.block, x.tile.groups,
+                                    (int32_t)k.chains.size(), dyn, st, a);
         if (e != hipSuccess) return hip_fail(e, "step kernel launch");
         if (ki >= 0) {
             ++prof_runs_now[ki];
@@ -1217,6 +1238,7 @@ int create_impl(pns_ctx** out, std::vector<ProblemSpec>& specs, int32_t mode, co
         }
         LaunchClass& K = ctx->classes[class_of[key]];
         K.dyn = std::max(K.dyn, dyn_lds(RR.exec.flav, RR.pitch));
+        K.n_max = std::max(K.n_max, RR.n);
         for (int32_t c = 0; c < S.chains; ++c) {
             ctx->h_chain_problem[c0 + c] = (int32_t)p;
             ctx->h_foff[c0 + c] = f0 + (int64_t)c * RR.pitch;
@@ -1471,6 +1493,7 @@ int reconfigure(pns_ctx* ctx, Tile t, int32_t n)
     K.tile = R.exec.tile;
     K.flav = R.exec.flav;
     K.dyn = dyn_lds(K.flav, R.pitch);
+    K.n_max = n;
     return reset_zero_state(ctx);
 }
 

@@ -7,6 +7,8 @@ import pytest
 from paper_2210_10513_amd import binding, inputs
 from paper_2210_10513_amd.binding import Sampler
 
+from test_gpu_full import _pair, _problem, _state
+
 pytestmark = pytest.mark.gpu
 
 
@@ -51,3 +53,19 @@ def test_kernel_of_an_open_tile(mode, kind, N, n, chains, log, flavours):
     (c,) = _classes(s)
     assert c["flavour"] in flavours
     s.close()
+
+
+# (the classes whose exact-time runs take the step kernel, and one beside each)
+@pytest.mark.parametrize("kind,N,n,chains", [("i64", 200, 24, 3), ("i64", 700, 64, 3), ("i64", 1000, 8, 300),
+                                             ("f32", 700, 4, 300), ("f32", 900, 4, 600), ("f32", 1500, 8, 600),
+                                             ("f32", 1500, 40, 600), ("f32", 6200, 4, 2), ("i16", 900, 4, 600)])
+def test_exact_time_runs_of_drawn_subsets(kind, N, n, chains):
+    """Between sampling runs, where the two kernels take turns: the step kernel's
+    records and states."""
+    Q, beta, layout = _problem(kind, N)
+    _pair(Q, beta, n, "basic", layout, chains, lambda s: _state(s.run(20).run_original(300).run(5)))
+
+
+def test_exact_time_runs_of_int64_fields():
+    Q, beta, layout = _problem("i64", 1100)
+    _pair(Q, beta, 0, "rf", layout, 600, lambda s: _state(s.run(10).run_original(40).run(5)))
