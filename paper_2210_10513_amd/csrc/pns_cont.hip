@@ -20,11 +20,12 @@
 // budget, the expected multiplicity) is then shared by 8 chains per wave
 // instruction instead of being repeated by a whole wave for one chain.  The
 // state, its log-density and the budget stay in registers for the whole
-// launch, the estimator sums in LDS (up to three dimensions) or registers.  Normal offsets: Box-Muller on two uniforms of one
-// Philox block, counter (chain, set index low, set index high, 0x80000000 |
-// j << 8 | t) for coordinates 2t, 2t + 1.  Step uniforms: those of the
-// discrete samplers (counter (chain, step low, step high, 0)), drawn 8 steps at
-// a time (lane r of a group holds step k + r).
+// launch, the estimator sums in LDS (up to three dimensions) or registers.
+// Normal offsets: Box-Muller on two uniforms of one Philox block, counter
+// (chain, set index low, set index high, 0x80000000 | j << 8 | t) for
+// coordinates 2t, 2t + 1.  Step uniforms: those of the discrete samplers (counter
+// (chain, step low, step high, 0)), drawn 8 steps at a time (lane r of a group
+// holds step k + r).
 //
 // Bound: VALU issue (a wave instruction takes four cycles of its SIMD; the
 // SIMDs issue in over 90% of them).  At d = 2, 25 pairs, L0 = 1000 a step of a
@@ -59,7 +60,6 @@ constexpr int kChainsPerBlock = 256 / kGroup;
 // Coordinates of offset pair `pj` of set `set`: Box-Muller, z0 = sqrt(-2 log
 // u1) cos(2 pi u2) for coordinate 2t and z1 = sqrt(-2 log u1) sin(2 pi u2) for
 // 2t + 1, u1 in (0, 1] from words 0, 1 and u2 in [0, 1) from words 2, 3.
-// Not inlined: the transcendental code stays out of the step loop's registers.
 template <int D>
 struct Offset {
     double v[D];
@@ -84,13 +84,12 @@ __device__ __forceinline__ Offset<D> draw_offset(uint64_t seed, uint32_t cid, in
 }
 
 // The expected multiplicity E[min(1 + G, L)] = (1 - (1 - p)^L) / p of a
-// budgeted record.  Not inlined: keeps the FP64 library code out of the step
-// loop's registers.
-__device__ __forceinline__ double mean_multiplicity(double p, double L)
+// budgeted record, lg = log(1 - p) for 0 < p < 1.
+__device__ __forceinline__ double mean_multiplicity(double p, double L, double lg)
 {
     if (p >= 1.0) return 1.0;
     if (p <= 0.0) return L;
-    return -expm1(L * log1p(-p)) / p;
+    return -expm1(L * lg) / p;
 }
 
 // Uniforms of step k of chain cid: log U1 (U1 in (0, 1], words 0, 1) and U2
@@ -142,7 +141,7 @@ __device__ __forceinline__ double group_scan(double v, int r)
 }
 
 // MP: neighbours per lane the kernel is built for (m <= MP; the launcher
-// picks the smallest of 2, 4, 7, 8 that holds m), so that the weights of a
+// picks the smallest of 1, 2, 4, 7, 8 that holds m), so that the weights of a
 // lane are straight-line code without branches and their exponentials
 // interleave.
 template <int D, int MP>
@@ -168,8 +167,8 @@ __global__ __launch_bounds__(256) void cont_kernel(const ContArgs a)
     // the eight, into sums of its own over the launch, added up over the group
     // at its end: the expected multiplicity (log1p, expm1, a division) and the
     // sums are then formed once per 8 steps instead of by every lane in every
-    // step.  Above three dimensions the 2 (4 D + 1) sums of a lane would not
-    // fit the registers, and the lanes share one set.
+    // step.  Above three dimensions the 2 (4 D + 1) sums of 256 lanes would take
+    // more than 64 KB of LDS, and the lanes share one set in registers.
     constexpr bool kDefer = D <= 3;
 
     double x[D], s[MP][D], w[MP];
@@ -181,27 +180,55 @@ __global__ __launch_bounds__(256) void cont_kernel(const ContArgs a)
     int64_t flips = 0, stays = 0;
 
     // New offsets for the groups whose lanes are set in `need` (whole groups;
-    // the same value in every lane).  A group's P pairs (at most 32) are drawn
-    // by 32 lanes of the wave, a pair per lane, two groups at a time, and
-    // handed to the group's lanes by lane reads.  (Drawn by the group's own 8
-    // lanes, each neighbour by itself, a set took ceil(2P / 8) Box-Muller
-    // passes of the whole wave, and each pair was drawn twice: at 25 pairs,
-    // two dimensions and L0 = 1000 about 1030 of the 1545 VALU instructions of
-    // a step, a wave of 8 chains drawing a set in every third step.)
+    // the same value in every lane).  One neighbour to a lane (P <= 4): each lane
+    // draws its own.  Two (P <= 8): each of the group's lanes draws a pair and the
+    // lanes read them from each other, every group at once.  More: a group's pairs
+    // are drawn by 16 (P <= 16) or 32 lanes of the wave, a pair per lane, four or
+    // two groups at a time, and handed to the group's lanes by lane reads.  (Drawn
+    // by the group's own 8 lanes, each neighbour by itself, a set took ceil(2P / 8)
+    // Box-Muller passes of the whole wave, and each pair was drawn twice: at 25
+    // pairs, two dimensions and L0 = 1000 about 1030 of the 1545 VALU instructions
+    // of a step, a wave of 8 chains drawing a set in every third step; by 32 lanes
+    // whatever the pairs, seven dimensions with 4 of them took 11.6 us per step
+    // of 8000 chains at L0 = 100 instead of 5.8.)
     auto load_sets = [&](uint64_t need) {
+        if constexpr (MP <= 2) {
+            if ((need >> gbase) & 1ull) {
+                const Offset<D> dl = draw_offset<D>(a.seed, cid, set, MP == 1 && r >= P ? r - P : r);
+#pragma unroll
+                for (int t = 0; t < MP; ++t) {
+                    const int j = r * MP + t;
+                    const int pj = j < P ? j : j - P;
+#pragma unroll
+                    for (int i = 0; i < D; ++i) {
+                        const double v = MP == 1 ? dl.v[i] : __shfl(dl.v[i], gbase + (pj & 7), 64);
+                        s[t][i] = j < n ? (j < P ? v : -v) : 0.0;
+                    }
+                }
+            }
+            return;
+        }
+        constexpr int kAtOnce = MP <= 4 ? 4 : 2, kLanes = 64 / kAtOnce;
         while (need != 0) {
-            const int ga = __builtin_ctzll(need);          // first lane of the first group
-            need &= ~(0xFFull << ga);
-            const int gb = need ? __builtin_ctzll(need) : ga;  // and of the second, if there is one
-            need &= ~(0xFFull << gb);
-            const int gl = lane < 32 ? ga : gb;
-            const int pl = lane & 31;
+            int first[kAtOnce];  // first lanes of the groups of this pass (the last one again where they are fewer)
+#pragma unroll
+            for (int q = 0; q < kAtOnce; ++q) {
+                first[q] = q == 0 || need != 0 ? __builtin_ctzll(need) : first[q > 0 ? q - 1 : 0];
+                need &= ~(0xFFull << first[q]);
+            }
+            int gl = first[0], base = 0;
+            bool mine = false;
+#pragma unroll
+            for (int q = 0; q < kAtOnce; ++q) {
+                gl = lane / kLanes == q ? first[q] : gl;
+                base = gbase == first[q] ? q * kLanes : base;
+                mine = mine || gbase == first[q];
+            }
+            const int pl = lane & (kLanes - 1);
             const uint32_t qcid = (uint32_t)__shfl((int)cid, gl, 64);
             const int slo = __shfl((int)(uint32_t)set, gl, 64), shi = __shfl((int)((uint64_t)set >> 32), gl, 64);
             const int64_t qset = (int64_t)(((uint64_t)(uint32_t)shi << 32) | (uint32_t)slo);
             const Offset<D> dl = draw_offset<D>(a.seed, qcid, qset, pl);
-            const bool mine = gbase == ga || gbase == gb;
-            const int base = gbase == ga ? 0 : 32;
 #pragma unroll
             for (int t = 0; t < MP; ++t) {
                 const int j = r * m + t;
@@ -209,7 +236,7 @@ __global__ __launch_bounds__(256) void cont_kernel(const ContArgs a)
                 const bool on = t < m && j < n;
 #pragma unroll
                 for (int i = 0; i < D; ++i) {
-                    const double v = __shfl(dl.v[i], base + (pj & 31), 64);
+                    const double v = __shfl(dl.v[i], base + (pj & (kLanes - 1)), 64);
                     if (mine) s[t][i] = on ? (j < P ? v : -v) : 0.0;
                 }
             }
@@ -245,7 +272,7 @@ __global__ __launch_bounds__(256) void cont_kernel(const ContArgs a)
     }
     // Sums of the records kept by the lanes (lane r: step kb + r, r < dcnt).
     auto flush = [&](int64_t kb) {
-        const double wrb = mean_multiplicity(dp, dL);
+        const double wrb = mean_multiplicity(dp, dL, dp > 0.0 && dp < 1.0 ? log1p(-dp) : 0.0);
         const bool on = r < dcnt;
         const double wM = on ? dM : 0.0, wR = on ? wrb : 0.0;
         auto add = [&](int u, double v) { dsum[kDefer ? u : 0][kDefer ? threadIdx.x : 0] += v; };
@@ -298,16 +325,22 @@ __global__ __launch_bounds__(256) void cont_kernel(const ContArgs a)
         const double p = S / (double)n;
         const double logU1 = __shfl(logU1b, gbase + bl, 64), U2 = __shfl(U2b, gbase + bl, 64);
         // (the estimate of the step kernel: the exact logarithm only where it
-        // cannot tell the floor or the order against L)
-        double q;
-        if (p >= 1.0) q = 0.0;
-        else if (p <= 0.0) q = INFINITY;
-        else q = step::geometric_quotient(logU1, p, (double)L);
+        // cannot tell the floor or the order against L; where the expected
+        // multiplicity is formed in the step, its logarithm serves both)
+        double q, wrb = 0.0;
+        if constexpr (kDefer) {
+            if (p >= 1.0) q = 0.0;
+            else if (p <= 0.0) q = INFINITY;
+            else q = step::geometric_quotient(logU1, p, (double)L);
+        } else {
+            const double lg = p > 0.0 && p < 1.0 ? log1p(-p) : 0.0;
+            q = p >= 1.0 ? 0.0 : p <= 0.0 ? INFINITY : logU1 / lg;
+            wrb = mean_multiplicity(p, (double)L, lg);
+        }
         const bool stay = q >= (double)L;
         const int64_t M = stay ? L : (int64_t)floor(q) + 1;
 
         // the record (J_k, M_k): estimator sums over the state before the move
-        double wrb = 0.0;
         if constexpr (kDefer) {
             const bool keep = r == bl;
 #pragma unroll
@@ -317,7 +350,6 @@ __global__ __launch_bounds__(256) void cont_kernel(const ContArgs a)
             dL = keep ? (double)L : dL;
             dcnt = bl + 1;
         } else {
-            wrb = mean_multiplicity(p, (double)L);
 #pragma unroll
             for (int u = 0; u < NA; ++u) {
                 if (akind[u] < 0) continue;
@@ -440,6 +472,7 @@ hipError_t launch_cont(const ContArgs& a, bool init, hipStream_t st)
 #define PNS_CONT_CASE(DD)                                                                                \
     case DD:                                                                                             \
         if (init) hipLaunchKernelGGL(cont::cont_init_kernel<DD>, grid_init, dim3(256), 0, st, a);        \
+        else if (m <= 1) hipLaunchKernelGGL((cont::cont_kernel<DD, 1>), grid_run, dim3(256), 0, st, a);  \
         else if (m <= 2) hipLaunchKernelGGL((cont::cont_kernel<DD, 2>), grid_run, dim3(256), 0, st, a);  \
         else if (m <= 4) hipLaunchKernelGGL((cont::cont_kernel<DD, 4>), grid_run, dim3(256), 0, st, a);  \
         else if (m <= 7) hipLaunchKernelGGL((cont::cont_kernel<DD, 7>), grid_run, dim3(256), 0, st, a);  \

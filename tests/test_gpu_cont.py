@@ -67,6 +67,17 @@ def test_records_match_oracle(d, sigma, pairs, L0, C):
     assert stays > 0 and stays < C * K
 
 
+# both sides of the lines where the lanes that draw a set change (one neighbour a
+# lane, a pair a lane, 16 and 32 lanes a set), with sets that run out in few and
+# in all of a wave's groups, the last wave not full
+@pytest.mark.parametrize("pairs", [1, 4, 5, 8, 9, 16, 17, 32])
+@pytest.mark.parametrize("d,L0", [(2, 3), (3, 60), (4, 3), (7, 60)])
+def test_sets_drawn_by_any_number_of_lanes(pairs, d, L0):
+    x0 = inputs.donut_draws(21, d, 9.0, 0.8, seed=pairs + d)
+    kw = dict(mu0=9.0, sigma=0.8, pairs=pairs, L0=L0, seed=13)
+    _compare(_gpu(x0, 150, **kw), x0, 150, **kw)
+
+
 def test_launches_continue_where_they_stopped_and_start_far_from_the_ring():
     """Three launches of 300 records equal one oracle run of 900; chains
     start at the origin (log pi = -mu0^2 / (2 sigma^2)) and at large radii;
