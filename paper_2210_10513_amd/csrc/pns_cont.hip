@@ -270,17 +270,19 @@ __global__ __launch_bounds__(256) void cont_kernel(const ContArgs a)
             acc[u] = akind[u] >= 0 ? a.sums[(int64_t)ch * 2 * NS + idx] : 0.0;
         }
     }
-    // Sums of the records kept by the lanes (lane r: step kb + r, r < dcnt).
-    auto flush = [&](int64_t kb) {
+    // Sums of the records kept by the lanes (lane r: step kb + r, r < dcnt; all
+    // eight but at the run's end).
+    auto flush = [&](int64_t kb, auto end) {
         const double wrb = mean_multiplicity(dp, dL, dp > 0.0 && dp < 1.0 ? log1p(-dp) : 0.0);
-        const bool on = r < dcnt;
+        const bool on = !decltype(end)::value || r < dcnt;
         const double wM = on ? dM : 0.0, wR = on ? wrb : 0.0;
         auto add = [&](int u, double v) { dsum[kDefer ? u : 0][kDefer ? threadIdx.x : 0] += v; };
         add(0, wM);
         add(NS, wR);
 #pragma unroll
         for (int i = 0; i < (kDefer ? D : 0); ++i) {
-            const double v = dx[i], v2 = v * v, v4 = v2 * v2;
+            // (a lane without a record holds an older one's state, whose power may be infinite)
+            const double v = on ? dx[i] : 0.0, v2 = v * v, v4 = v2 * v2;
             add(1 + i, wM * v);
             add(NS + 1 + i, wR * v);
             add(1 + D + i, wM * v2);
@@ -301,7 +303,7 @@ __global__ __launch_bounds__(256) void cont_kernel(const ContArgs a)
         const int bl = (int)(it & (kGroup - 1));
         if (bl == 0) {
             if constexpr (kDefer) {
-                if (it > 0) flush(k - kGroup);
+                if (it > 0) flush(k - kGroup, std::false_type{});
             }
             const Uniforms u = step_uniforms(cid, k + r, a.seed);
             logU1b = u.logU1;
@@ -420,7 +422,7 @@ __global__ __launch_bounds__(256) void cont_kernel(const ContArgs a)
     }
 
     if constexpr (kDefer) {
-        if (dcnt > 0) flush(k0 + a.steps - dcnt);
+        if (dcnt > 0) flush(k0 + a.steps - dcnt, std::true_type{});
     }
 
     // chain state back to memory

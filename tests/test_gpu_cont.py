@@ -176,3 +176,18 @@ def test_log_ring_shorter_than_a_batch_of_steps(d, K, ring):
         assert np.array_equal(g["action"][:, k % ring], o.action[:, k])
         assert np.array_equal(g["M"][:, k % ring], o.M[:, k])
         assert np.allclose(g["w"][:, k % ring], o.w[:, k], rtol=P_RTOL, atol=0)
+
+
+def test_sums_of_states_whose_power_overflows():
+    """A run that ends inside a batch of eight steps, from states whose fourth
+    power is infinite: that sum is infinite, not NaN (0 times infinity of the
+    lanes without a record), the others are finite."""
+    from paper_2210_10513_amd.binding import ContSampler
+    x0 = np.full((3, 2), 1e100)
+    s = ContSampler(3, dim=2, x0=x0, pairs=5, sigma=0.5, L0=30, seed=2).run(9)
+    sums = s.read_sums()
+    s.close()
+    power4 = sums[:, :, 5:7]
+    assert np.isposinf(power4).all()
+    rest = np.delete(sums, (5, 6), axis=2)
+    assert np.isfinite(rest).all() and (rest[:, 0, 0] >= 9).all()
