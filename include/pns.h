@@ -171,7 +171,8 @@ typedef struct pns_problem_info {
 
 /* Result of pns_autotune. */
 typedef struct pns_tune {
-    int32_t block;
+    int32_t block;          /* 0, 0: the tile left open (opts.block = 0), which runs
+                               a kernel of the library's choice                  */
     int32_t groups;
     int32_t subset_size;
     int32_t trials;         /* timed configurations                              */
@@ -241,14 +242,18 @@ int pns_create_batch(pns_ctx** out, int32_t num_problems, const pns_problem* pro
  * tile whose capacity 4 * block * groups lies between N and twice N rounded
  * up to 256 (tiles of 32 or more fields per lane only where a window kernel
  * runs the problem; where a window-kernel tile holds the problem, only the
- * smallest such tile), with every subset size 16, 32, ... up to N/2, is run
- * for trial_steps steps (after a warmup; the faster of two timed runs) from
- * x = 0 with max(3072, opts->num_chains) chains, at most 4096 (the
+ * smallest such tile; where an open tile runs a kernel of the library's choice
+ * (all bits, drawn subsets), that kernel instead of the tiles it stands for,
+ * and the result is block = groups = 0), with every subset size 16, 32, ... up
+ * to N/2, is run for trial_steps steps (after a warmup; the faster of two timed
+ * runs) from x = 0 with max(3072, opts->num_chains) chains, at most 4096 (the
  * problem's betas repeated), so that the device is loaded as in a real run;
  * the largest subset size whose rate is within 10% of the best trial is
  * chosen, on its fastest tile (Sec 5: on parallel hardware, take the largest
- * affordable partial neighbor set).  Results are cached per process by (N,
- * dtype, layout, mode, n, chains, trial_steps).  Synchronises the device.
+ * affordable partial neighbor set).  A context created with the result's block,
+ * groups and subset size (and as many chains) runs the kernel that was timed.
+ * Results are cached per process by (N, dtype, layout, mode, n, chains,
+ * trial_steps).  Synchronises the device.
  * Errors: as pns_create.
  */
 int pns_autotune(const void* Q, int32_t N, double beta, int32_t subset_size, int32_t mode, const pns_opts* opts,

@@ -9,6 +9,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -16,6 +17,7 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <set>
 #include <string>
 #include <thread>
 #include <type_traits>
@@ -1584,14 +1586,15 @@ int autotune_impl(const ProblemSpec& base, int32_t mode, const pns_opts& o, int3
     if (prep) preps.push_back(prep);
     int rc = create_impl(&ctx, one, mode, t, preps);
     if (rc) return rc;
-    // Every (tile, subset size): tiles that hold N in at most twice its
-    // rounded size, wide tiles only where the subset runs a window kernel.
+    // Every (kernel that runs, subset size): tiles that hold N in at most twice
+    // its rounded size, wide tiles only where the subset runs a window kernel.
     struct Trial {
         Tile tile;
         int32_t n;
         double rate, frate;
     };
     std::vector<Trial> res;
+    std::set<std::array<int32_t, 4>> tried;
     int trials = 0;
     // Where a window kernel tile holds the problem, only the smallest such
     // tile is tried (over the subset sizes): the window kernel ran faster than
@@ -1615,17 +1618,19 @@ int autotune_impl(const ProblemSpec& base, int32_t mode, const pns_opts& o, int3
         if (window_cap && (int64_t)tl.block * 4 * tl.groups != window_cap) continue;
         for (int32_t n : ns) {
             const int32_t fl = flavour_for(mode, base.N, n, tl, ctx->qtype, ctx->htype);
-            // (every table tile of these runs the same kernel, see exec_of)
-            const Tile def = default_tile(base.N);
-            if ((fl == 0 || fl == 2) && (tl.block != def.block || tl.groups != def.groups)) continue;
             if (fl < 0 || (wide_tile(tl) && fl != 3 && fl != 4 && fl != 5)) continue;
             if (window_cap && fl != 5) continue;
+            // (where the library's choice runs instead of the tile, it is the same
+            // for every tile: timed once, and returned as an open tile)
+            const Exec x = exec_of(tl, fl, false, base.N, n, ctx->qtype, ctx->htype, mode, false, false, ctx->num_chains);
+            if (!tried.insert({x.tile.block, x.tile.groups, x.flav, n}).second) continue;
+            const bool open = x.flav != fl || x.tile.block != tl.block || x.tile.groups != tl.groups;
             double r = 0.0, fr = 0.0;
             rc = reconfigure(ctx, tl, n);
             if (!rc) rc = time_config(ctx, trial_steps, &r, &fr);
             if (rc) break;
             ++trials;
-            res.push_back({tl, n, r, fr});
+            res.push_back({open ? Tile{0, 0} : tl, n, r, fr});
         }
         if (rc) break;
     }
