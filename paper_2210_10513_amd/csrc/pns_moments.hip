@@ -6,7 +6,8 @@
 //   on the matrix cores.  Integer weights: v_mfma_i32_16x16x64_i8, x as 0/1
 //   bytes and m_k as digits base 128, a pass over the records per digit (the
 //   first digit of all of them, a further one only of the steps of 64 records
-//   that have it), so that every sum is exact.  Real weights:
+//   that have it), so that the sums of a workgroup are exact and an entry of G
+//   below 2^53 is.  Real weights:
 //   v_mfma_f32_16x16x32_bf16 with FP32 accumulation, each weight split into
 //   three bf16 pieces.
 // * log Z = log sum_x exp(-beta x^T Q x) by enumeration of all 2^N states
@@ -241,8 +242,10 @@ __global__ __launch_bounds__(256) void pack_kernel(const uint8_t* __restrict__ X
 // and one mask per four records).  B = x; A = x times the weights' digit: a
 // digit d < 128 under the mask 0x80 - x, which is 0x7F where x = 1 and keeps
 // nothing of d where x = 0.  The int32 sums are exact (127 per record); the
-// waves add theirs, times 128^digit, into the tile in LDS (FP64, exact
-// integers below 2^53), and the tile goes to part[chunk][tile].
+// waves add theirs, times 128^digit, into the tile in LDS, five digits in 64-bit
+// integers (below 2^31 2^28 (1 + 1 / 127) in each of four waves: exact, in any
+// order), then, if a weight has more, the other four; the tile goes to
+// part[chunk][tile] in FP64.
 // Bound: VALU issue: a step of a wave is 130 VALU instructions (60 for A, 28
 // for B) and 16 MFMAs, 580 issue cycles against 256 of the matrix cores, two
 // waves to a SIMD.  N = 512, K = 131072, weights below 128: 31 us, and 42 with
@@ -250,6 +253,7 @@ __global__ __launch_bounds__(256) void pack_kernel(const uint8_t* __restrict__ X
 // the bf16 product of the same weights took 150 us, with 277 VALU instructions
 // per 32 records and a load's latency in every step.  The whole call 218 -> 59
 // us; K = 32768, N = 20 (8 steps a workgroup instead of 16 a wave) 83 -> 30.
+constexpr int kLowDigits = 5;
 constexpr int kLd = kTile + 2;  // LDS row of the tile: rows 4 apart on other banks
 
 __global__ __launch_bounds__(256, 2) void moments_i8_kernel(const uint32_t* __restrict__ Xb, int32_t npad, int64_t steps,
@@ -257,7 +261,7 @@ __global__ __launch_bounds__(256, 2) void moments_i8_kernel(const uint32_t* __re
                                                          const uint8_t* __restrict__ ndig, int64_t chunk_steps,
                                                          int32_t tiles, double* __restrict__ part)
 {
-    __shared__ double tile[kTile * kLd];
+    __shared__ unsigned long long tile[kTile * kLd];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int t = (int)(blockIdx.x % (unsigned)tiles);
     const int64_t c = blockIdx.x / (unsigned)tiles;
@@ -271,16 +275,15 @@ __global__ __launch_bounds__(256, 2) void moments_i8_kernel(const uint32_t* __re
     const int64_t w1 = w0 + quarter < s1 ? w0 + quarter : s1;
     const int l16 = lane & 15, kg = lane >> 4;
     const int sh = 4 * (kg & 1);
-    for (int e = threadIdx.x; e < kTile * kLd; e += 256) tile[e] = 0.0;
+    for (int e = threadIdx.x; e < kTile * kLd; e += 256) tile[e] = 0;
     // digits of this wave's largest weight
     int nd = 0;
     for (int64_t s = w0 + lane; s < w1; s += 64) nd = max(nd, (int)ndig[s]);
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) nd = max(nd, __shfl_xor(nd, d, 64));
-    __syncthreads();
+    const bool more = __syncthreads_or(nd > kLowDigits) != 0;  // (of any wave)
 
-    double scale = 1.0;
-    for (int p = 0; p < nd; ++p, scale *= 128.0) {
+    auto pass = [&](int p, int shift) {
         i32x4 acc[4][4];
 #pragma unroll
         for (int a = 0; a < 4; ++a)
@@ -344,12 +347,24 @@ __global__ __launch_bounds__(256, 2) void moments_i8_kernel(const uint32_t* __re
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
                     if (p == 0 || acc[a][b][e] != 0)
-                        atomicAdd(&tile[(a * 16 + kg * 4 + e) * kLd + b * 16 + l16], scale * (double)acc[a][b][e]);
-    }
-    __syncthreads();
+                        atomicAdd(&tile[(a * 16 + kg * 4 + e) * kLd + b * 16 + l16],
+                                  (unsigned long long)(uint32_t)acc[a][b][e] << shift);
+    };
     double* dst = part + (c * tiles + t) * (int64_t)(kTile * kTile);
     auto place = [](int i) { return (i & 3) * 16 + (i >> 2); };  // row or column i in the order of the MFMA tiles
-    for (int e = threadIdx.x; e < kTile * kTile; e += 256) dst[e] = tile[place(e / kTile) * kLd + place(e % kTile)];
+    auto sum = [&](int e) { return (double)tile[place(e / kTile) * kLd + place(e % kTile)]; };
+#pragma unroll 1
+    for (int p = 0; p < nd && p < kLowDigits; ++p) pass(p, 7 * p);
+    __syncthreads();
+    for (int e = threadIdx.x; e < kTile * kTile; e += 256) dst[e] = sum(e);
+    if (!more) return;
+    __syncthreads();
+    for (int e = threadIdx.x; e < kTile * kLd; e += 256) tile[e] = 0;
+    __syncthreads();
+#pragma unroll 1
+    for (int p = kLowDigits; p < nd; ++p) pass(p, 7 * (p - kLowDigits));
+    __syncthreads();
+    for (int e = threadIdx.x; e < kTile * kTile; e += 256) dst[e] += 34359738368.0 * sum(e);  // 128^5
 }
 
 // G[i][j] = f times the sum over chunks of the partial tiles (integer weights:

@@ -72,6 +72,31 @@ def test_moments_digits_of_the_weights(K, N):
     assert np.abs(G / wantf - 1.0).max() < 1e-12
 
 
+@pytest.mark.parametrize("bits", [34, 35, 36, 62])
+def test_moments_of_large_weights_round_once_per_half(bits):
+    """Weights on both sides of five digits, up to nine: the sums of a workgroup
+    are exact integers in two halves, so that the records of one (512) give G to
+    two roundings and one addition, and more records the same G in every run."""
+    from paper_2210_10513_amd import binding
+    rng = np.random.default_rng(bits)
+    K, N = 512, 70
+    X = (rng.random((K, N)) < 0.5).astype(np.uint8)
+    m = rng.integers(0, 2 ** bits, size=K, dtype=np.int64, endpoint=True)
+    G = np.zeros((N, N))
+    binding.pns_moments(X, m, G)
+    Xi = X.astype(object)
+    want = (Xi.T * m.astype(object)) @ Xi
+    for i in range(N):
+        for j in range(N):
+            assert abs(int(G[i, j]) - want[i, j]) * 2 ** 52 <= want[i, j]
+    X, m = np.tile(X, (20, 1)), np.tile(m, 20)
+    first = None
+    for _ in range(4):
+        binding.pns_moments(X, m, G)
+        first = G.copy() if first is None else first
+        assert np.array_equal(G, first)
+
+
 def test_moments_device_buffers_and_ldx():
     import torch
     from paper_2210_10513_amd import binding
