@@ -589,12 +589,17 @@ int max_side_streams()
 
 // Time of a step of `chains` chains of a class, in about us: the latency of a
 // step, or the throughput once the chip is full (int16 figures; the
-// comparison is between classes of one context).
+// comparison is between classes of one context).  The step kernel's windows: 1.8
+// (256 x 1), 2.35 (256 x 2, two groups), 2.15 (512 x 2), 2.9 and 3.3 (256 x 8,
+// compact and two groups); as the window kernel's the second was taken for
+// shorter than the third, and shared a queue with the first.
 double step_time(int32_t flav, Tile t, double chains)
 {
     const double waves = t.block / 64.0, log_waves = std::log2(waves), g = t.groups;
     const bool window = flav == 5 || flav == 1 || flav == 3 || flav == 4;
-    const double latency = window ? 1.4 + 0.07 * g + 0.2 * log_waves : 0.55 + 0.23 * g + 0.17 * log_waves;
+    const double latency = flav == 5 ? 1.4 + 0.07 * g + 0.2 * log_waves
+                           : window  ? 1.8 + 0.2 * g - 0.1 * log_waves + (flav == 4 ? 0.3 : 0.0)
+                                     : 0.55 + 0.23 * g + 0.17 * log_waves;
     const double each = window ? (9e-4 + 6e-5 * g) * waves : 2.7e-4 * waves * g;
     return std::max(latency, each * chains);
 }
