@@ -34,10 +34,6 @@ using step::kTabHi;
 using step::kTabLo;
 using step::kTabMax;
 
-// Flavour codes of this kernel in the launch classes.
-constexpr int FLAV_FULL = 6;   // every bit
-constexpr int FLAV_DRAW = 7;   // a drawn subset
-
 // Keys of the table of occurrences: draw number (falling), then position.
 constexpr int kPosBits = 20;
 constexpr uint32_t kDraws = (1u << (32 - kPosBits)) - 1u;
@@ -82,7 +78,10 @@ typedef const __attribute__((address_space(3))) double* LdsDouble;
 
 // Waves per SIMD asked of the compiler: as many as leave the plain kernels
 // without (or nearly without) spilled registers, one fewer for the kernels with
-// a budget.
+// a budget.  The tile of 512 x 8 has no fewer than two; its 32 64-bit fields a lane
+// spill 48 to 242 registers, and it is still ahead of the step kernel's 1024 x 4
+// (Rejection-Free floats, N = 10000, us per step: 64 chains 17.7 -> 11.7, 1024 chains
+// 87.9 -> 78.4) but for drawn subsets of floats.
 template <typename HT, int G, bool PLAIN>
 constexpr int waves_per_eu()
 {
@@ -879,32 +878,27 @@ hipError_t launch_one(int32_t grid, size_t dyn, hipStream_t st, const StepArgs& 
     return hipGetLastError();
 }
 
-// Tiles (workgroup size, 4-bit groups per lane); which runs what, and both sides
-// of each line measured: exec_of in pns_runtime.cpp.
-#define PNS_FULL_TILE_LIST(X, QT, HT) \
-    X(QT, HT, 64, 1)   \
-    X(QT, HT, 64, 2)   \
-    X(QT, HT, 64, 3)   \
-    X(QT, HT, 64, 4)   \
-    X(QT, HT, 128, 1)  \
-    X(QT, HT, 256, 1)  \
-    X(QT, HT, 256, 2)  \
-    X(QT, HT, 256, 3)  \
-    X(QT, HT, 256, 4)  \
-    X(QT, HT, 512, 1)  \
-    X(QT, HT, 512, 2)  \
-    X(QT, HT, 512, 3)  \
-    X(QT, HT, 512, 4)  \
-    X(QT, HT, 512, 8)
+#define PNS_FULL_CASE(B, GG)                                                             \
+    if (block == B && groups == GG)                                                      \
+        return instr ? launch_one<QT, HT, B / 64, GG, DRAWN, true>(grid, dyn, st, a)     \
+                     : launch_one<QT, HT, B / 64, GG, DRAWN, false>(grid, dyn, st, a);
 
-#define PNS_FULL_DISPATCH_TILE(QT, HT, B, GG)                                                     \
-    if (block == B && groups == GG) {                                                             \
-        if (drawn)                                                                                \
-            return instr ? full::launch_one<QT, HT, B / 64, GG, true, true>(grid, dyn, st, a)     \
-                         : full::launch_one<QT, HT, B / 64, GG, true, false>(grid, dyn, st, a);   \
-        return instr ? full::launch_one<QT, HT, B / 64, GG, false, true>(grid, dyn, st, a)        \
-                     : full::launch_one<QT, HT, B / 64, GG, false, false>(grid, dyn, st, a);      \
+// The tiles of a field type and of all bits or drawn subsets (pns_internal.h).
+template <typename QT, typename HT, bool DRAWN>
+hipError_t launch_tile(bool instr, int block, int groups, int grid, size_t dyn, hipStream_t st, const StepArgs& a)
+{
+    if constexpr (std::is_floating_point<HT>::value) {
+        if constexpr (DRAWN) { PNS_FULL_TILES_F64_DRAWN(PNS_FULL_CASE) }
+        else { PNS_FULL_TILES_F64_ALL(PNS_FULL_CASE) }
+    } else if constexpr (sizeof(HT) == 8) {
+        if constexpr (DRAWN) { PNS_FULL_TILES_I64_DRAWN(PNS_FULL_CASE) }
+        else { PNS_FULL_TILES_I64_ALL(PNS_FULL_CASE) }
+    } else {
+        if constexpr (DRAWN) { PNS_FULL_TILES_I32_DRAWN(PNS_FULL_CASE) }
+        else { PNS_FULL_TILES_I32_ALL(PNS_FULL_CASE) }
     }
+    return hipErrorInvalidConfiguration;
+}
 
 }  // namespace full
 }  // namespace pns

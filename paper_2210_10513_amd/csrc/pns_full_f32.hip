@@ -7,8 +7,8 @@ namespace pns {
 hipError_t launch_full_f32(bool drawn, bool instr, int block, int groups, int grid, size_t dyn, hipStream_t st,
                            const StepArgs& a)
 {
-    PNS_FULL_TILE_LIST(PNS_FULL_DISPATCH_TILE, float, double)
-    return hipErrorInvalidConfiguration;
+    return drawn ? full::launch_tile<float, double, true>(instr, block, groups, grid, dyn, st, a)
+                 : full::launch_tile<float, double, false>(instr, block, groups, grid, dyn, st, a);
 }
 
 }  // namespace pns

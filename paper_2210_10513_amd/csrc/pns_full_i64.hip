@@ -7,8 +7,8 @@ namespace pns {
 hipError_t launch_full_i64(bool drawn, bool instr, int block, int groups, int grid, size_t dyn, hipStream_t st,
                            const StepArgs& a)
 {
-    PNS_FULL_TILE_LIST(PNS_FULL_DISPATCH_TILE, int32_t, int64_t)
-    return hipErrorInvalidConfiguration;
+    return drawn ? full::launch_tile<int32_t, int64_t, true>(instr, block, groups, grid, dyn, st, a)
+                 : full::launch_tile<int32_t, int64_t, false>(instr, block, groups, grid, dyn, st, a);
 }
 
 }  // namespace pns

@@ -32,6 +32,26 @@ struct Problem {
 // subset (pns_full.h).
 constexpr int32_t kFlavFull = 6, kFlavDraw = 7;
 
+// Its tiles X(workgroup size, 4-bit groups per lane) by field type, over all bits
+// and over drawn subsets: those that exec_of in pns_runtime.cpp chooses.
+#define PNS_FULL_TILES_COMMON(X) \
+    X(64, 1) X(64, 2) X(64, 3) X(256, 1) X(256, 2) X(256, 3) X(512, 1) X(512, 2) X(512, 3) X(512, 4)
+#define PNS_FULL_TILES_I32_ALL(X) PNS_FULL_TILES_COMMON(X) X(64, 4) X(512, 8)
+#define PNS_FULL_TILES_I32_DRAWN(X) PNS_FULL_TILES_COMMON(X) X(64, 4) X(256, 4) X(512, 8)
+#define PNS_FULL_TILES_F64_ALL(X) PNS_FULL_TILES_COMMON(X) X(128, 1) X(512, 8)
+#define PNS_FULL_TILES_F64_DRAWN(X) PNS_FULL_TILES_COMMON(X) X(128, 1) X(64, 4) X(256, 4)
+#define PNS_FULL_TILES_I64_ALL(X) X(512, 1) X(256, 2) X(512, 2) X(512, 3) X(512, 4) X(512, 8)
+#define PNS_FULL_TILES_I64_DRAWN(X) PNS_FULL_TILES_I64_ALL(X) X(64, 1) X(128, 1) X(256, 1)
+
+inline bool have_full_tile(int32_t htype, bool drawn, int32_t block, int32_t groups)
+{
+#define PNS_TILE_IS(B, G) || (block == B && groups == G)
+    if (htype == H_F64) return drawn ? (false PNS_FULL_TILES_F64_DRAWN(PNS_TILE_IS)) : (false PNS_FULL_TILES_F64_ALL(PNS_TILE_IS));
+    if (htype == H_I64) return drawn ? (false PNS_FULL_TILES_I64_DRAWN(PNS_TILE_IS)) : (false PNS_FULL_TILES_I64_ALL(PNS_TILE_IS));
+    return drawn ? (false PNS_FULL_TILES_I32_DRAWN(PNS_TILE_IS)) : (false PNS_FULL_TILES_I32_ALL(PNS_TILE_IS));
+#undef PNS_TILE_IS
+}
+
 // Everything a step kernel launch needs.  Chain c of the context stores its
 // state at field offset foff[c] (fields x, h, rand-set membership) and at
 // index c in the per-chain arrays.

@@ -415,6 +415,8 @@ Exec exec_of(Tile tile, int32_t flav, bool asked, int32_t N, int32_t n, int32_t 
     else if (N <= 4096) t = few || i64 || !drawn ? Tile{512, 2} : Tile{256, 4};
     else if (N <= 6144) t = {512, 3};
     else if (N <= 8192) t = {512, 4};
+    // (the lists of pns_internal.h hold what is chosen here)
+    if (!have_full_tile(htype, drawn, t.block, t.groups)) return {tile, flav};
     return {t, drawn ? kFlavDraw : kFlavFull};
 }
 
