@@ -69,3 +69,12 @@ def test_exact_time_runs_of_drawn_subsets(kind, N, n, chains):
 def test_exact_time_runs_of_int64_fields():
     Q, beta, layout = _problem("i64", 1100)
     _pair(Q, beta, 0, "rf", layout, 600, lambda s: _state(s.run(10).run_original(40).run(5)))
+
+
+@pytest.mark.parametrize("kind,N", [("i16", 13400), ("i64", 13400), ("i16", 16384)])
+def test_widest_drawn_subsets(kind, N):
+    """The table of occurrences past 64 KB of LDS (tables and members with it)."""
+    Q, beta, layout = _problem(kind, N)
+    _pair(Q, beta, 700, "basic", layout, 2, lambda s: _state(s.run(20), log=True), log_capacity=20)
+    if kind == "i16":
+        _pair(Q, beta, 90, "unbiased_rand", layout, 2, lambda s: _state(s.run(20), log=True), log_capacity=20, L0=30)

@@ -71,3 +71,25 @@ def test_log_partition_of_entries_that_are_not_finite(N, i, j):
         Q[j, i] = np.nan
         assert binding.pns_log_partition(Q, 0.7, layout=binding.PNS_UPPER) == \
             binding.pns_log_partition(U, 0.7, layout=binding.PNS_UPPER)
+
+
+@pytest.mark.parametrize("dtype", [np.int16, np.float32])
+@pytest.mark.parametrize("N", [28, 29, 31, 32])
+def test_log_partition_where_waves_take_several_assignments(dtype, N):
+    """From 29 bits on a wave takes more than one assignment of its bits: closed
+    forms (no energy; the bits by themselves) and blocks of coupled bits, the
+    highest among them, whose log Z add up."""
+    rng = np.random.default_rng(N)
+    beta = 0.3
+    lz = lambda Q: binding.pns_log_partition(Q.astype(dtype), beta)
+    assert abs(lz(np.zeros((N, N))) - N * np.log(2.0)) <= 1e-13 * N * N
+    d = rng.integers(-9, 10, N).astype(np.float64)
+    want = np.log1p(np.exp(-beta * d)).sum()
+    assert abs(lz(np.diag(d)) - want) <= 1e-13 * N * max(1.0, abs(want))
+    Q, want = np.zeros((N, N)), 0.0
+    for lo, hi in ((0, 5), (5, 13), (13, 20), (20, N)):
+        B = np.triu(rng.integers(-5, 6, (hi - lo, hi - lo))).astype(np.float64)
+        B = B + np.triu(B, 1).T
+        Q[lo:hi, lo:hi] = B
+        want += _log_z(B, beta, False)
+    assert abs(lz(Q) - want) <= 1e-13 * N * max(1.0, abs(want))
