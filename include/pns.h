@@ -547,8 +547,9 @@ int pns_load(pns_ctx* ctx, const void* buf, int64_t size);
  *          any host buffer makes it synchronise the stream before it
  *          returns.
  * Computed on the int8 matrix cores: x as 0/1 bytes, m_k as digits base 128,
- * exact int32 sums per digit, put together in FP64: G is exact while every
- * entry is below 2^53 (beyond that each addition of a partial sum rounds once).
+ * exact int32 sums per digit, put together in 64-bit integers per workgroup and
+ * in FP64 over them: G is exact while every entry is below 2^53 (beyond that a
+ * workgroup's sum rounds twice and each addition of one once, in a fixed order).
  * Errors: PNS_EINVAL (NULL X, m or G, N outside [1, 32768], K < 0,
  * ldx < N), PNS_ENOMEM, PNS_EDEVICE.
  */
@@ -597,11 +598,13 @@ int pns_moments_f64(const uint8_t* X, int64_t ldx, const double* w, int64_t K, i
  *   - X, m, G and sum_m (or NULL) must be device memory (PNS_EINVAL
  *     otherwise): nothing is staged, and the call only queues work on
  *     `stream`;
- *   - the workspace (weight pieces, packed records, partial tiles) is a
- *     static 68 MiB array on each GPU, held until the process ends; a call
- *     whose workspace would exceed it is refused with PNS_EINVAL (about
- *     K * N / 8 bytes of packed records plus 16 KiB per 64 x 64 tile of the
- *     upper triangle; K = 131072 records of N = 512 fit);
+ *   - the workspace (digits of the weights, packed records, partial tiles) is a
+ *     static 68 MiB array on each GPU, held until the process ends; calls of up
+ *     to 32 MiB are taken, counted as K * N / 8 bytes of packed records (N rounded
+ *     up to 64), 6 bytes a record for its weight and 16 KiB per 64 x 64 tile of the
+ *     upper triangle, others refused with PNS_EINVAL (K = 131072 records of N =
+ *     512 fit).  What a call uses of the array is more than that count, at most
+ *     the 68 MiB: 9 bytes a record and 32 KiB a tile;
  *   - every call on a GPU uses that GPU's one workspace: calls that overlap
  *     on one GPU (other streams, other threads) race and must be ordered by
  *     the caller.  The workspace keeps the last call's contents; each call

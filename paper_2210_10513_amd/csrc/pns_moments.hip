@@ -950,7 +950,7 @@ extern "C" int pns_moments_noalloc(const uint8_t* X, int64_t ldx, const int64_t*
     const size_t tile_bytes = (size_t)tiles * 64 * 64 * 4;
     if (fixed + tile_bytes > kCallBytes)
         return set_error(PNS_EINVAL,
-                         "K = %lld records of N = %d need %zu bytes of workspace; the static workspace holds %zu "
+                         "K = %lld records of N = %d count %zu bytes of workspace; calls of up to %zu are taken "
                          "(use pns_moments)",
                          (long long)K, N, fixed + tile_bytes, kCallBytes);
     const MomentsWorkspace w = moments_int_workspace(K, N, (int64_t)kScratchBytes);
