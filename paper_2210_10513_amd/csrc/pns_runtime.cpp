@@ -996,6 +996,17 @@ std::vector<double> energies_to_double(const pns_ctx* ctx, const std::vector<int
 int energies_out(const pns_ctx* ctx, double* dst, const int64_t* src, size_t count)
 {
     if (ctx->qtype == Q_F32) return dev_out(dst, src, count * 8);  // (their bits are doubles)
+    if (!is_device_ptr(dst)) {
+        // in place: as fast as the copy (3e6 energies 3.3 ms; through two fresh vectors,
+        // whose pages are touched for the first time, 11)
+        const int rc = dev_out(dst, src, count * 8);
+        for (size_t i = 0; rc == PNS_OK && i < count; ++i) {
+            int64_t e;
+            std::memcpy(&e, dst + i, 8);
+            dst[i] = (double)e;
+        }
+        return rc;
+    }
     std::vector<int64_t> bits;
     int rc = d2h(bits, src, count);
     if (rc) return rc;
