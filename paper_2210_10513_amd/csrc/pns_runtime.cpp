@@ -1030,11 +1030,14 @@ int rows_out(pns_ctx* ctx, void* dst, const void* src, size_t elem, bool by_pitc
     const size_t padded = (by_pitch ? (size_t)C * per * ctx->max_pitch : (size_t)ctx->fields) * elem;
     hipPointerAttribute_t attr{};
     const bool to_device = is_device_ptr(dst);
-    int now = 0;
-    HIP_TRY(hipGetDevice(&now), "current device");
-    // (another device's memory: through the host, as small rows)
-    const bool gather = now == ctx->device && C * per <= INT32_MAX && (!to_device || (hipPointerGetAttributes(&attr, dst) == hipSuccess &&
-                                                              attr.device == ctx->device));
+    bool gather = (to_device || total > kRowsSmall) && C * per <= INT32_MAX;
+    if (gather) {
+        // (another device's memory: through the host, as small rows)
+        int now = 0;
+        HIP_TRY(hipGetDevice(&now), "current device");
+        gather = now == ctx->device &&
+                 (!to_device || (hipPointerGetAttributes(&attr, dst) == hipSuccess && attr.device == ctx->device));
+    }
     RowGather a{src, dst, ctx->foff, ctx->offsets, last_action, ctx->chain_problem, ctx->problems,
                 by_pitch ? ctx->max_pitch : 0, per, 0};
     if (gather && to_device) {
@@ -1043,7 +1046,7 @@ int rows_out(pns_ctx* ctx, void* dst, const void* src, size_t elem, bool by_pitc
         if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
         return e == hipSuccess ? PNS_OK : hip_fail(e, "rows to device buffer");
     }
-    if (gather && total > kRowsSmall) {
+    if (gather) {
         std::lock_guard<std::mutex> lock(ctx->rows_mutex);
         size_t widest = 0;
         for (const ProblemRun& R : ctx->probs) widest = std::max(widest, (size_t)R.N * per * elem);
@@ -1085,7 +1088,9 @@ int rows_out(pns_ctx* ctx, void* dst, const void* src, size_t elem, bool by_pitc
             if (last_action && la[c] >= 0) to[la[c]] ^= 1u;
         }
     }
-    return copy_out(dst, out.data(), total);
+    if (to_device) return copy_out(dst, out.data(), total);
+    std::memcpy(dst, out.data(), total);
+    return PNS_OK;
 }
 
 // Everything a context needs, for one or several problems.
