@@ -105,9 +105,10 @@ typedef struct pns_opts {
                                steps of a pns_run in one launch                   */
     int32_t block;          /* threads per workgroup (one workgroup per chain);
                                0 = chosen from the tuned table (all-bits and
-                               drawn-subset problems then run a kernel and
-                               workgroup of the library's choice, with the same
-                               records; pns_class_profile names it).  Step-kernel
+                               drawn-subset problems and systematic windows of
+                               integers may then run a kernel and workgroup of
+                               the library's choice, with the same records;
+                               pns_class_profile names it).  Step-kernel
                                tiles (block x groups): 64x1, 64x2, 64x4, 128x1,
                                128x2, 128x4, 256x1, 256x2, 256x4, 256x8, 512x2,
                                512x4, 1024x2, 1024x4, and 256x16 for 32-bit fields
@@ -218,14 +219,14 @@ int pns_create(pns_ctx** out, const void* Q, int32_t N, double beta, int32_t sub
  * method (QUBOs of uneven N, each with its own chains and temperatures):
  * chain c of problem p is numbered problems[0..p-1].num_chains + c.  Problems
  * are grouped by workgroup tile and kernel flavour; each group (launch class)
- * runs in its own kernel launch, the launches concurrent on side streams (in
- * the graph form as parallel graph nodes): one stream per class, up to the
- * process's hardware queues (GPU_MAX_HW_QUEUES, read when HIP starts; at most
- * 16), classes packed longest first when there are more.  The streams start
- * largest workgroups first, and in launches of 4096 steps or more those of
- * one-wave classes 200 us after the others (a one-wave delay kernel on the
- * context's stream), so that workgroups of several waves find whole compute
- * units.
+ * runs in its own kernel launch, the launches concurrent on the context's
+ * stream and on side streams (in the graph form as parallel graph nodes): one
+ * stream per class, up to the process's hardware queues (GPU_MAX_HW_QUEUES,
+ * read when HIP starts) but the null stream's, at most 15; classes packed
+ * longest first when there are more.  The streams start largest workgroups
+ * first, and in launches of 4096 steps or more those of one-wave classes 200 us
+ * after the others (a one-wave delay kernel on the first of their streams), so
+ * that workgroups of several waves find whole compute units.
  * Per-chain arrays of bits or fields (pns_read, pns_read_current,
  * pns_read_snapshots) are concatenated, chain c occupying the N of its
  * problem; pns_chain_offsets gives the offsets.  Histograms are not
@@ -442,10 +443,11 @@ int pns_read_ladder(pns_ctx* ctx, int32_t* ladder);
 /*
  * Recompute every chain's local fields h = offdiag(Q) x and energy x^T Q x
  * from its current state, overwriting the incrementally maintained values:
- * H = X A for all chains of a problem as one matrix product on the matrix
- * cores (integer Q on the int8 cores, split into bytes, exact; float Q on the
- * FP64 cores), the computation that also gives the initial fields on
- * creation.  Integer fields are exact either way; float32 Q fields are
+ * H = X A for all chains of a problem as one matrix product on the int8
+ * matrix cores (integer Q split into bytes, float Q into the bytes of 39-bit
+ * fixed-point numbers, exact sums; what float entries hold below those, and
+ * rows with many such entries, in FP64), the computation that also gives the
+ * initial fields on creation.  Integer fields are exact either way; float32 Q fields are
  * accumulated in FP64 each flip, so their drift over 1e5 flips stays near
  * FP64 rounding, and a refresh resets it.  States, step counters and the
  * last record are unchanged.  Asynchronous on the context's stream.
